@@ -18,7 +18,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblancet_moe.so")
-SOURCES = ["api.cpp", "block.cpp", "plan.cpp", "gate.hip", "route.hip", "gemm.hip", "attn.hip", "norm.hip"]
+SOURCES = ["api.cpp", "block.cpp", "plan.cpp", "gate.hip", "route.hip", "gemm.hip", "gemm_256x256.hip",
+           "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip", "norm.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -49,7 +50,7 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-ASM_READ_SOURCES = ["gemm.hip", "attn.hip"]  # kernels that read LDS through inline asm
+ASM_READ_SOURCES = ["gemm_256x256.hip", "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip"]  # kernels that read LDS through inline asm
 
 
 def _check_isa(src: str, verbose: bool) -> None:

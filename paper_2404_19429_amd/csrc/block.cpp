@@ -213,7 +213,7 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       const int64_t t0 = Tc * i;
       HIP_TRY(hipStreamWaitEvent(Sc, ev_disp[i], 0));
       const int32_t* rb = i == 0 ? nullptr : A.fill + (int64_t)(i - 1) * E;
-      launch_expert_fwd(mc, A.send_buf, rb, A.fill + (int64_t)i * E, W1p, W2p, A.H, A.A, A.expert_out, wsb + L.sk, Sc);
+      launch_expert_fwd(pc, A.send_buf, rb, A.fill + (int64_t)i * E, W1p, W2p, A.H, A.A, A.expert_out, wsb + L.sk, Sc);
       HIP_TRY(hipGetLastError());
       HIP_TRY(order(Sc, Sx));
       launch_combine(pc, A.expert_out, A.idx + t0 * k, A.slot + t0 * k, A.w + t0 * k, bfm(out, t0 * d), Sx,

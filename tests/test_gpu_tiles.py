@@ -1,0 +1,100 @@
+"""Tile shapes of the bf16 expert products.
+
+Which shape a product runs on depends on the sizes alone, and every shape sums
+the same 32-wide K steps in order, so with ksplit = 0 a batch cut into
+partitions -- whose products run on smaller tiles than the whole batch's --
+gives the whole batch's bits, forward and dX.  The cases put row counts and
+widths on both sides of the tiles' edges (64, 128, 256 rows; a last column tile
+of 64), down to a few rows per expert.  The weight-gradient products on both of
+their shapes are compared with a float32 product of their own inputs.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from synth import LayerSpec, layer_inputs
+from tests.gpu_harness import ebuf, host, kept_rows, log, nan_fill, run_layer, spec_C, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def L():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2404_19429_amd import lancet_moe
+    return lancet_moe
+
+
+def _s(T, d, f, E, k, **kw):
+    return LayerSpec(**{**dict(name="tiles", T=T, d=d, f=f, E=E, k=k, cf_num=5, cf_den=4, dtype="bf16",
+                               act="gelu_tanh", renorm=1 if k > 1 else 0, seed=71), **kw})
+
+
+# (spec, partitions): 16 -> 2 rows per expert; k = E fixes the row counts (every
+# expert gets every token), so 130 / 65 rows stand just past an edge and 258 /
+# 129 / 86 likewise; f = 192 and 320 leave a half-empty last 128-column tile.
+CASES = {
+    "few_rows": (_s(64, 64, 192, 8, 2), 8),
+    "rows_130_65_edges": (_s(130, 192, 320, 4, 4), 2),
+    "rows_258_129_86_edges": (_s(258, 128, 832, 2, 2), 3),
+    "skewed": (_s(1536, 128, 1024, 16, 2, zipf_s=1.2, cf_num=1, cf_den=1), 4),
+    "large_then_small": (_s(4096, 64, 2048, 8, 2, act="relu"), 32),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_partitions_on_smaller_tiles_are_bitwise_the_whole_batch(L, case):
+    spec, n = CASES[case]
+    inp = layer_inputs(spec)
+    C = spec_C(spec)
+    log(f"[tiles] {case}: T={spec.T} in {n} partitions, C={C}")
+    whole, dev = run_layer(L, spec, inp, C, ksplit=0)
+    Tc = spec.T // n
+    cfg = L.make_cfg(Tc, spec.d, spec.f, spec.E, spec.k, C, 1, spec.dtype, spec.act, spec.renorm, ksplit=0)
+    b = L.alloc_layer(whole.cfg)
+    nan_fill(b)
+    bias = None if inp["bias"] is None else torch.as_tensor(inp["bias"]).cuda()
+    fills = [torch.zeros(spec.E, dtype=torch.int32, device="cuda")]
+    L.moe_pack_weights(cfg, dev["W1"], dev["W2"], b.W1p, b.W2p)
+    for i in range(n):
+        sl = slice(i * Tc, (i + 1) * Tc)
+        fills.append(torch.empty(spec.E, dtype=torch.int32, device="cuda"))
+        x, idx, w, slot = dev["x"][sl].clone(), b.idx[sl].clone(), b.w[sl].clone(), b.slot[sl].clone()
+        logits, y, dl, dx = b.logits[sl].clone(), b.y[sl].clone(), b.dlogits[sl].clone(), b.dx[sl].clone()
+        L.moe_gate_topk(cfg, x, dev["Wg"], bias, logits, idx, w)
+        L.moe_dispatch(cfg, x, idx, fills[i], fills[i + 1], slot, b.send_buf, b.ws_dispatch)
+        L.moe_expert_ffn_fwd(cfg, b.send_buf, fills[i], fills[i + 1], b.W1p, b.W2p, b.H, b.A, b.O, b.ws_ffn)
+        L.moe_combine(cfg, b.O, idx, slot, w, y)
+        L.moe_bwd_dx(cfg, dev["Wg"], logits, idx, w, slot, fills[i], fills[i + 1], b.H, b.O, b.W1p, b.W2p,
+                     dev["dy"][sl].clone(), b.dO, b.dH, b.dXe, dl, dx, b.ws_dx)
+        b.y[sl], b.dx[sl] = y, dx
+    torch.cuda.synchronize()
+    fill = host(whole.fill)
+    np.testing.assert_array_equal(host(fills[-1]), fill)
+    for name in ("H", "A", "O", "dH", "dXe"):
+        np.testing.assert_array_equal(kept_rows(ebuf(b, name), fill), kept_rows(ebuf(whole, name), fill), err_msg=name)
+    for name in ("y", "dx"):
+        np.testing.assert_array_equal(host(getattr(b, name)), host(getattr(whole, name)), err_msg=name)
+
+
+@pytest.mark.parametrize("T,d,f,E,k", [(37, 64, 192, 4, 2), (300, 320, 192, 2, 2), (1100, 1088, 2112, 16, 2)],
+                         ids=["few_rows", "column_remainders", "more_than_512_large_tiles"])
+def test_weight_gradients_on_both_tile_shapes(L, T, d, f, E, k):
+    """dW2 = dO^T A and dW1 = dH^T X against float32 products of the kernel's own
+    bf16 inputs: two float sums of n terms (each within gamma_n sum|a||b|, u =
+    2^-24) and one bf16 rounding (half an ulp, 2^-8 of the value)."""
+    spec = _s(T, d, f, E, k)
+    b, _ = run_layer(L, spec, layer_inputs(spec), spec_C(spec))
+    fill = host(b.fill)
+    bufs = {n: ebuf(b, n) for n in ("dO", "A", "dH", "send_buf")}
+    for e in range(E):
+        n = int(fill[e])
+        for name, l, r in (("dW2", "dO", "A"), ("dW1", "dH", "send_buf")):
+            a, c = (torch.from_numpy(np.ascontiguousarray(bufs[q][e, :n])).cuda().double() for q in (l, r))
+            ref, mag = a.t() @ c, a.abs().t() @ c.abs()
+            got = getattr(b, name)[e].double()
+            bound = 2 * n * 2.0 ** -24 * mag + 2.0 ** -8 * ref.abs()
+            assert bool(((got - ref).abs() <= bound + 1e-30).all()), f"{name} of expert {e}"
