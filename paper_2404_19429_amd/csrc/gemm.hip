@@ -17,7 +17,7 @@
 // The same kernel serves dense products (one group, no row ranges): the
 // block's projections and, with row-major operands split into token ranges,
 // their weight gradients.
-// f32 path: a plain LDS-tiled FMA GEMM with the same addressing.
+// f32 path: LDS-tiled float MFMAs with the same addressing.
 #include "internal.h"
 #include "gemm_wide.h"
 
@@ -27,102 +27,202 @@
 
 namespace lmoe {
 
-template <typename OutT> __device__ __forceinline__ void store_out(OutT* p, float v);
-template <> __device__ __forceinline__ void store_out<uint16_t>(uint16_t* p, float v) { *p = (uint16_t)f32_to_bf16_bits(v); }
-template <> __device__ __forceinline__ void store_out<float>(float* p, float v) { *p = v; }
-template <typename OutT> __device__ __forceinline__ float load_out(const OutT* p);
-template <> __device__ __forceinline__ float load_out<uint16_t>(const uint16_t* p) { return bf16_bits_to_f32(*p); }
-template <> __device__ __forceinline__ float load_out<float>(const float* p) { return *p; }
+// ------------------------------------------------------------------ f32 path
+// v_mfma_f32_16x16x4_f32 over LDS tiles, float in, float accumulation.  Bound:
+// the matrix cores' float rate (157 TFLOP/s nominal); an MFMA takes 32 cycles
+// for two 4-byte operands per lane, so plain loads (global -> registers -> LDS,
+// one stage ahead) and LDS reads hide under it.  Training step of 2000 tokens
+// (d 512, f 2048, 8 experts, one MI355X), against a 64 x 64 tile of vector
+// multiply-adds: H 191 -> 113 us, expert_out 358 -> 125, each dW 146 -> 104 (81
+// TFLOP/s); a 128-tile was slower on all but dW (its ragged rows and rounds).
+//
+// A block is 2 x 2 waves of WT x WT fragments of 16 x 16: a tile of 32 WT on a
+// side, 64 / WT of K per stage (the same 16 KB of LDS and four 16-byte loads
+// per thread and stage for either WT).  The MFMA adds its four products to the
+// accumulator one fused multiply-add at a time in K order (measured: the same
+// bits as a loop of fmaf), and every element takes its K in ascending order, so
+// results do not depend on WT and are those of the plain sum.
+// The product is computed transposed: a lane ends with four consecutive output
+// columns of one row.
+template <int WT, bool KC>
+struct F32Tile {
+  static constexpr int ROWS = 32 * WT, BK = 64 / WT;   // rows or columns of the operand; K per stage
+  static constexpr int LD = KC ? BK + 4 : ROWS + 16;   // padded LDS row: a wave's reads spread over the banks
+  static constexpr int ELEMS = (KC ? ROWS : BK) * LD;
+  static constexpr int NLD = ROWS * BK / 4 / 256;      // 16-byte loads per thread and stage
+  static constexpr int W = KC ? BK / 4 : ROWS / 4;     // chunks per LDS row
+  const float* rp[NLD];                                // the thread's row (KC) or column of chunk i, at K = 0
+  // KC: [ROWS][K] from row r0 < rlim; else [K][ROWS] from column r0.  Rows or
+  // columns past the limit repeat the last (their outputs are not stored).
+  __device__ void plan(const float* base, int64_t ld, int r0, int rlim) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int c = threadIdx.x + 256 * i;
+      if constexpr (KC) rp[i] = base + min(r0 + c / W, rlim - 1) * ld;
+      else rp[i] = base + min(r0 + 4 * (c % W), rlim - 4);
+    }
+  }
+  __device__ static int kofs(int i) { return KC ? 4 * ((threadIdx.x + 256 * i) % W) : (threadIdx.x + 256 * i) / W; }
+  // The stage at k0, from addresses clamped into K (klim > 0): without a branch
+  // every load of the stage is in flight together.
+  __device__ void load(f32x4 (&v)[NLD], int64_t ld, int k0, int klim) const {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int k = min(k0 + kofs(i), klim - (KC ? 4 : 1));
+      v[i] = *reinterpret_cast<const f32x4*>(rp[i] + (KC ? k : k * ld));
+    }
+  }
+  // To LDS, K at and past klim as zeros.  KC: within 16 of K, k = 4 s + q goes
+  // to place 4 q + s, so that a lane's elements of four MFMAs are one 16-byte read.
+  __device__ static void store(const f32x4 (&v)[NLD], float* st, int k0, int klim) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int c = threadIdx.x + 256 * i;
+      const f32x4 x = k0 + kofs(i) < klim ? v[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (KC) {
+        float* o = st + c / W * LD + (c % W >> 2) * 16 + (c & 3);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[4 * q] = x[q];
+      } else {
+        *reinterpret_cast<f32x4*>(st + c / W * LD + 4 * (c % W)) = x;
+      }
+    }
+  }
+  // The lane's elements of the four MFMAs of the stage's 16-K block kb (K 4 s + lane / 16
+  // for MFMA s) for row or column r16 + lane % 16.
+  __device__ static f32x4 frag(const float* st, int r16, int kb, int lane) {
+    const int r = r16 + (lane & 15), q = lane >> 4;
+    if constexpr (KC) {
+      return *reinterpret_cast<const f32x4*>(st + r * LD + 16 * kb + 4 * q);
+    } else {
+      const float* o = st + (16 * kb + q) * LD + r;
+      return f32x4{o[0], o[4 * LD], o[8 * LD], o[12 * LD]};
+    }
+  }
+};
 
-template <int EPI, typename OutT>
-__device__ __forceinline__ void epilogue_store(const GemmParams& p, int64_t off, float v) {
-  OutT* C = (OutT*)p.C;
+template <int EPI>
+__device__ __forceinline__ void f32_store(const GemmParams& p, int64_t off, const f32x4& v) {
+  f32x4 o = v;
+  if constexpr (EPI == EPI_DACT) {
+    const f32x4 h = *reinterpret_cast<const f32x4*>((const float*)p.Aux + off);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = v[u] * act_bwd(h[u], p.act);
+  }
+  *reinterpret_cast<f32x4*>((float*)p.C + off) = o;
   if constexpr (EPI == EPI_FWD1) {
-    store_out<OutT>(C + off, v);
-    store_out<OutT>((OutT*)p.C2 + off, act_fwd(v, p.act));
-  } else if constexpr (EPI == EPI_DACT) {
-    const float h = load_out<OutT>((const OutT*)p.Aux + off);
-    store_out<OutT>(C + off, v * act_bwd(h, p.act));
-  } else {
-    store_out<OutT>(C + off, v);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = act_fwd(v[u], p.act);
+    *reinterpret_cast<f32x4*>((float*)p.C2 + off) = o;
   }
 }
 
-// ------------------------------------------------------------------ f32 path
-template <bool B_K, bool RAGGED_K, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int g = blockIdx.z;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  int lo, span;
-  group_rows(p, g, lo, span);
-  int Mlim, Klim;
+// Ragged-M: the tiles of the rows that are there, n fastest, fall into eight
+// contiguous ranges, one per XCD (block index modulo 8), so an XCD's L2 holds
+// the operands its blocks share and every XCD has the same number of tiles.
+// Ragged-K (tiles as long as their group): rows of tn tiles are dealt to the
+// XCDs in turn, so a few large experts still spread over the chip.
+template <int WT, bool B_K, bool RAGGED_K, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int tm, int tn, int groups) {
+  using TA = F32Tile<WT, !RAGGED_K>;
+  using TB = F32Tile<WT, B_K && !RAGGED_K>;
+  constexpr int BM = TA::ROWS, BK = TA::BK;
+  __shared__ __attribute__((aligned(16))) float As[2][TA::ELEMS];
+  __shared__ __attribute__((aligned(16))) float Bs[2][TB::ELEMS];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+  int g, m0, n0, lo, span;
   if constexpr (RAGGED_K) {
-    Mlim = p.M;
-    Klim = span;
+    const int tr = (local / tn) * 8 + xcd;
+    if (tr >= groups * tm) return;
+    g = tr / tm;
+    m0 = (tr - g * tm) * BM;
+    n0 = (local % tn) * BM;
+    group_rows(p, g, lo, span);
   } else {
-    Mlim = span;
-    Klim = p.K;
-    if (m0 >= Mlim) return;
+    const WPrefix P = wide_tile_prefix<BM, false, false>(p, lane, groups, tm, tn);
+    const int per = (P.NF + 7) / 8, t = xcd * per + local;
+    if (local >= per || t >= P.NF) return;
+    g = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < groups && P.incl <= t)));
+    const int q = t - __builtin_amdgcn_readlane(P.excl, g);
+    m0 = q / tn * BM;
+    n0 = q % tn * BM;
+    lo = __builtin_amdgcn_readlane(P.lo, g);
+    span = __builtin_amdgcn_readlane(P.span, g);
   }
+  const int Mlim = RAGGED_K ? p.M : span, Klim = RAGGED_K ? span : p.K;
+  if (m0 >= Mlim) return;
   const float* Ab = (const float*)p.A + g * p.sA + (int64_t)lo * p.lda;
   const float* Bb = (const float*)p.B + g * p.sB + (RAGGED_K ? (int64_t)lo * p.ldb : 0);
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < Klim; k0 += BK) {
-    for (int i = tid; i < BM * BK; i += 256) {
-      int m, k;
-      float a = 0.f;
-      if constexpr (RAGGED_K) {
-        k = i / BM; m = i % BM;
-        if (m0 + m < Mlim && k0 + k < Klim) a = Ab[(int64_t)(k0 + k) * p.lda + m0 + m];
-      } else {
-        m = i / BK; k = i % BK;
-        if (m0 + m < Mlim && k0 + k < Klim) a = Ab[(int64_t)(m0 + m) * p.lda + k0 + k];
-      }
-      As[k][m] = a;
+  const int wm = (wid >> 1) * 16 * WT, wn = (wid & 1) * 16 * WT;
+  f32x4 acc[WT][WT];
+#pragma unroll
+  for (int i = 0; i < WT; ++i)
+#pragma unroll
+    for (int j = 0; j < WT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 va[TA::NLD], vb[TB::NLD];
+  TA ta;
+  TB tb;
+  ta.plan(Ab, p.lda, m0, Mlim);
+  tb.plan(Bb, p.ldb, n0, p.N);
+  if (Klim > 0) {
+    ta.load(va, p.lda, 0, Klim);
+    tb.load(vb, p.ldb, 0, Klim);
+  }
+  int buf = 0;
+  for (int k0 = 0; k0 < Klim; k0 += BK, buf ^= 1) {
+    TA::store(va, As[buf], k0, Klim);
+    TB::store(vb, Bs[buf], k0, Klim);
+    __syncthreads();   // this stage is in LDS; every wave is past the stage before (the other buffer)
+    // The next stage's loads, in flight under this stage's MFMAs (past the last
+    // stage: one that is not stored).  The opaque start keeps the compiler from
+    // moving them to their use at the top of the loop.
+    int kn = k0 + BK;
+    asm volatile("" : "+s"(kn));
+    ta.load(va, p.lda, kn, Klim);
+    tb.load(vb, p.ldb, kn, Klim);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int KB = BK / 16;
+    f32x4 fa[KB][WT], fb[KB][WT];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int i = 0; i < WT; ++i) fa[kb][i] = TA::frag(As[buf], wm + 16 * i, kb, lane);
+#pragma unroll
+      for (int j = 0; j < WT; ++j) fb[kb][j] = TB::frag(Bs[buf], wn + 16 * j, kb, lane);
     }
-    for (int i = tid; i < BN * BK; i += 256) {
-      int n, k;
-      float b = 0.f;
-      if constexpr (B_K && !RAGGED_K) {
-        n = i / BK; k = i % BK;
-        if (n0 + n < p.N && k0 + k < Klim) b = Bb[(int64_t)(n0 + n) * p.ldb + k0 + k];
-      } else {
-        k = i / BN; n = i % BN;
-        if (n0 + n < p.N && k0 + k < Klim) b = Bb[(int64_t)(k0 + k) * p.ldb + n0 + n];
-      }
-      Bs[k][n] = b;
-    }
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);   // the stage's reads together, ahead of its MFMAs
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+        for (int i = 0; i < WT; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+          for (int j = 0; j < WT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[kb][j][s], fa[kb][i][s], acc[i][j], 0, 0, 0);
   }
   const int64_t cbase = (int64_t)g * p.sC + (RAGGED_K ? 0 : (int64_t)lo * p.ldc);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
+  for (int i = 0; i < WT; ++i) {
+    const int row = m0 + wm + 16 * i + (lane & 15);
     if (row >= Mlim) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col < p.N) epilogue_store<EPI, float>(p, cbase + (int64_t)row * p.ldc + col, acc[i][j]);
+    for (int j = 0; j < WT; ++j) {
+      const int col = n0 + wn + 16 * j + 4 * (lane >> 4);
+      if (col < p.N)   // (N is a multiple of 8)
+        f32_store<EPI>(p, cbase + (int64_t)row * p.ldc + col, acc[i][j]);
     }
   }
+}
+
+template <int WT, bool B_K, bool RAGGED_K, int EPI>
+static void launch_f32(const GemmParams& p, int groups, int64_t rows, int cols, hipStream_t s) {
+  // (ragged-M: with up to 15 alignment rows, as wide_tile_prefix counts them)
+  const int tm = (int)((rows + (RAGGED_K ? 0 : 15) + 32 * WT - 1) / (32 * WT)), tn = (cols + 32 * WT - 1) / (32 * WT);
+  const int64_t blocks = RAGGED_K ? ((int64_t)groups * tm + 7) / 8 * 8 * tn : ((int64_t)groups * tm * tn + 7) / 8 * 8;
+  hipLaunchKernelGGL((gemm_f32_kernel<WT, B_K, RAGGED_K, EPI>), dim3((unsigned)blocks), dim3(256), 0, s, p, tm, tn,
+                     groups);
 }
 
 // --------------------------------------------------------------- launchers
@@ -186,15 +286,27 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
 template <bool B_K, bool RAGGED_K, int EPI>
 static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s) {
   if (rows <= 0 || cols <= 0 || c.E <= 0) return;
-  if (c.dtype != MOE_BF16) {
-    dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64), (unsigned)c.E);
-    hipLaunchKernelGGL((gemm_f32_kernel<B_K, RAGGED_K, EPI>), grid, dim3(256), 0, s, p);
-    return;
-  }
   // Rows a group is expected to hold: the call's assignments spread evenly (T is
   // only a hint here: rows may come from elsewhere).
   const double expect = c.T > 0 ? std::min<double>(c.C, (double)c.T * c.k / c.E) : c.C;
-  run_wide_any(WideCall{kind, c.act, c.E, rows, cols, expect, std::sqrt(expect * (1. - (double)c.k / c.E)), p}, s);
+  const double spread = std::sqrt(expect * (1. - (double)c.k / c.E));
+  if (c.dtype != MOE_BF16) {
+    // The tile whose busiest CU has the least work: tiles per CU times area, the
+    // 32-tile's extra loads per flop counted as 30 %.
+    // Measured, 64-tile against 32-tile: expert_out of 2000 tokens (d 512, f
+    // 2048, 8 experts) 136 and 125 us, its H 113 and 123; dW of 63 tokens (d 640,
+    // f 1280, 8 experts) 15 and 23, its H 24 and 15.
+    auto cost = [&](int t, double f) {
+      const double n = RAGGED_K ? std::ceil((double)rows / t)
+                                : 0.5 * (std::ceil(std::max(1., expect - spread) / t) + std::ceil((expect + spread) / t));
+      return std::ceil(c.E * n * std::ceil((double)cols / t) / num_cus()) * t * t * f;
+    };
+    const bool fits = (double)c.E * ((rows + 46) / 32) * ((cols + 31) / 32) <= 1 << 22;   // bounds the grid
+    if (fits && cost(32, 1.3) < cost(64, 1.)) launch_f32<1, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
+    else launch_f32<2, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
+    return;
+  }
+  run_wide_any(WideCall{kind, c.act, c.E, rows, cols, expect, spread, p}, s);
 }
 
 // Rows per expert block of an [E][C][*] buffer (C rounded up to 16 for bf16).
