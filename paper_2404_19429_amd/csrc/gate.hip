@@ -44,7 +44,7 @@ template <> __device__ __forceinline__ double elem_f64<float>(const u32x4& v, in
 
 constexpr int kGateGroup = 4;   // chunks whose loads are in flight together
 
-template <typename T, int MT, int NT, int NWV>
+template <typename T, int MT, int NT, int NWV, int KT>
 __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict__ x, const T* __restrict__ Wg,
                                                             const float* __restrict__ bias,
                                                             float* __restrict__ logits, int32_t* __restrict__ idx,
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict
   constexpr int V = Vec<T>::N;          // elements per 16-byte load
   constexpr int CW = 4 * V;             // columns per chunk (four lane groups)
   constexpr int TM = 16 * MT;           // tokens per block
-  __shared__ double red[NWV - 1][MT][NT][4][kWave];
+  __shared__ double red[NWV][MT * NT * 4 * kWave];
   __shared__ float lg[TM][kMaxE + 1];
 
   const int lane = threadIdx.x & 63;
@@ -122,34 +122,24 @@ __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict
     }
   }
 
-  // Wave sums meet in wave order.  Accumulator element r of a lane holds
-  // row q + 4r, column i16 of its 16 x 16 tile: token mt*16 + q + 4r, expert
-  // nt*16 + i16.
-  if (wid > 0) {
+  // Wave sums meet in LDS and are added in wave order, every thread its share.
+  // Accumulator element r of a lane holds row q + 4r, column i16 of its 16 x 16
+  // tile: token mt*16 + q + 4r, expert nt*16 + i16.
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wid - 1][mt][nt][r][lane] = acc[mt][nt][r];
-  }
+      for (int r = 0; r < 4; ++r) red[wid][((mt * NT + nt) * 4 + r) * kWave + lane] = acc[mt][nt][r];
   __syncthreads();
-  if (wid == 0) {
+  for (int o = threadIdx.x; o < MT * NT * 4 * kWave; o += 64 * NWV) {
+    const int l = o & 63, r = (o >> 6) & 3, t = o >> 8;
+    const int e = (t % NT) * 16 + (l & 15);
+    if (e >= E) continue;
+    double s = red[0][o];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int e = nt * 16 + i16;
-        if (e >= E) continue;
-        const double b = bias ? (double)bias[e] : 0.0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          double s = acc[mt][nt][r];
-#pragma unroll
-          for (int w = 0; w < NWV - 1; ++w) s += red[w][mt][nt][r][lane];
-          lg[mt * 16 + q + 4 * r][e] = (float)(s + b);
-        }
-      }
+    for (int w = 1; w < NWV; ++w) s += red[w][o];
+    lg[(t / NT) * 16 + (l >> 4) + 4 * r][e] = (float)(s + (bias ? (double)bias[e] : 0.0));
   }
   __syncthreads();
 
@@ -157,62 +147,95 @@ __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict
   const int64_t ntok = (T_tokens - t0) < TM ? (T_tokens - t0) : TM;
   for (int i = threadIdx.x; i < ntok * E; i += blockDim.x) logits[t0 * E + i] = lg[i / E][i % E];
 
-  // Top-k by (logit desc, expert asc), one thread per token.
-  if (threadIdx.x < ntok) {
-    const int tl = threadIdx.x;
-    uint64_t best[kMaxK];
+  // Top-k by (logit desc, expert asc): four lanes per token scan every fourth
+  // expert into sorted lists of KT keys (distinct: the expert is part of the
+  // key), which two exchanges merge, so each lane ends with the token's list.
+  const int tl = threadIdx.x >> 2, l4 = threadIdx.x & 3;
+  if (tl < ntok) {
+    uint64_t best[KT];
 #pragma unroll
-    for (int r = 0; r < kMaxK; ++r) best[r] = 0ull;
-    for (int e = 0; e < E; ++e) {
-      uint64_t key = ((uint64_t)float_order_key(lg[tl][e]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)e);
+    for (int r = 0; r < KT; ++r) best[r] = 0ull;
+    auto insert = [&](uint64_t key) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < kMaxK; ++r) {
-        if (r < k && key > best[r]) {
-          const uint64_t tmp = best[r];
-          best[r] = key;
-          key = tmp;
-        }
+      for (int r = 0; r < KT; ++r) {
+        const uint64_t hi = key > best[r] ? key : best[r];
+        key = key > best[r] ? best[r] : key;
+        best[r] = hi;
       }
+    };
+    for (int e = l4; e < E; e += 4)
+      insert(((uint64_t)float_order_key(lg[tl][e]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)e));
+#pragma unroll
+    for (int o = 1; o <= 2; o <<= 1) {
+      uint64_t other[KT];
+#pragma unroll
+      for (int r = 0; r < KT; ++r) other[r] = __shfl_xor(best[r], o, kWave);
+#pragma unroll
+      for (int r = 0; r < KT; ++r) insert(other[r]);
     }
     const float m = float_from_order_key((uint32_t)(best[0] >> 32));
-    float denom = 0.f;
-    if (renorm) {
+    float ex[KT], denom = 0.f;
 #pragma unroll
-      for (int r = 0; r < kMaxK; ++r)
-        if (r < k) denom += expf(float_from_order_key((uint32_t)(best[r] >> 32)) - m);
-    } else {
-      for (int e = 0; e < E; ++e) denom += expf(lg[tl][e] - m);
+    for (int r = 0; r < KT; ++r) {
+      ex[r] = expf(float_from_order_key((uint32_t)(best[r] >> 32)) - m);
+      if (r < k) denom += ex[r];
+    }
+    if (!renorm) {
+      denom = 0.f;
+      for (int e = l4; e < E; e += 4) denom += expf(lg[tl][e] - m);
+      denom += __shfl_xor(denom, 1, kWave);
+      denom += __shfl_xor(denom, 2, kWave);
     }
     const int64_t t = t0 + tl;
 #pragma unroll
-    for (int r = 0; r < kMaxK; ++r) {
-      if (r < k) {
-        const int be = (int)(0xffffffffu - (uint32_t)(best[r] & 0xffffffffu));
-        const float bl = float_from_order_key((uint32_t)(best[r] >> 32));
-        idx[t * k + r] = be;
-        wout[t * k + r] = expf(bl - m) / denom;
+    for (int r = 0; r < KT; ++r) {
+      if (r < k && (r & 3) == l4) {
+        idx[t * k + r] = (int)(0xffffffffu - (uint32_t)(best[r] & 0xffffffffu));
+        wout[t * k + r] = ex[r] / denom;
       }
     }
   }
 }
 
-template <typename T, int MT, int NT, int NWV>
-static void launch_gate_e(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
+template <typename T, int MT, int NT, int NWV, int KT>
+static void launch_gate_k(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
                           int32_t* idx, float* w, hipStream_t s) {
   const int64_t blocks = (c.T + 16 * MT - 1) / (16 * MT);
-  hipLaunchKernelGGL((gate_topk_kernel<T, MT, NT, NWV>), dim3((unsigned)blocks), dim3(64 * NWV), 0, s,
+  hipLaunchKernelGGL((gate_topk_kernel<T, MT, NT, NWV, KT>), dim3((unsigned)blocks), dim3(64 * NWV), 0, s,
                      (const T*)x, (const T*)Wg, bias, logits, idx, w, c.T, c.d_model, c.E, c.k, c.renorm);
 }
+// 32 tokens per block; 16 where 32 would leave fewer than two blocks per CU (the
+// kernel is then latency: loads, a short MFMA chain, the sums, the selection).
+// One MI355X, with the wave sums spread over the block and four lanes per token
+// selecting (before: one wave summing, one lane per token with a list of eight):
+// 2048 tokens, d 768, 8 experts 11.3 -> 6.2 us; 8192 tokens, d 1024, 32 experts
+// 22.5 -> 16.3; 32768 tokens, 64 experts 123 -> 101; 16384 tokens, d 2048, 8
+// experts 28.6 -> 28.0 (fp64 matrix rate).
+template <typename T, int NT, int NWV, int KT>
+static void launch_gate_m(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
+                          int32_t* idx, float* w, hipStream_t s) {
+  if (c.T < (int64_t)32 * 2 * num_cus()) launch_gate_k<T, 1, NT, NWV, KT>(c, x, Wg, bias, logits, idx, w, s);
+  else launch_gate_k<T, 2, NT, NWV, KT>(c, x, Wg, bias, logits, idx, w, s);
+}
+// KT: the top-k list's length, k rounded up to 1, 2, 4 or 8.
+template <typename T, int NT, int NWV>
+static void launch_gate_e(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
+                          int32_t* idx, float* w, hipStream_t s) {
+  if (c.k == 1) launch_gate_m<T, NT, NWV, 1>(c, x, Wg, bias, logits, idx, w, s);
+  else if (c.k == 2) launch_gate_m<T, NT, NWV, 2>(c, x, Wg, bias, logits, idx, w, s);
+  else if (c.k <= 4) launch_gate_m<T, NT, NWV, 4>(c, x, Wg, bias, logits, idx, w, s);
+  else launch_gate_m<T, NT, NWV, 8>(c, x, Wg, bias, logits, idx, w, s);
+}
 
-// 32 tokens per block; d is split over 8 waves (4 when four expert tiles
-// already give each wave independent accumulators and more registers).
+// d is split over 8 waves (4 when four expert tiles already give each wave
+// independent accumulators and more registers).
 template <typename T>
 static void launch_gate_t(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
                           int32_t* idx, float* w, hipStream_t s) {
-  if (c.E <= 16) launch_gate_e<T, 2, 1, 8>(c, x, Wg, bias, logits, idx, w, s);
-  else if (c.E <= 32) launch_gate_e<T, 2, 2, 8>(c, x, Wg, bias, logits, idx, w, s);
-  else if (c.E <= 48) launch_gate_e<T, 2, 3, 4>(c, x, Wg, bias, logits, idx, w, s);
-  else launch_gate_e<T, 2, 4, 4>(c, x, Wg, bias, logits, idx, w, s);
+  if (c.E <= 16) launch_gate_e<T, 1, 8>(c, x, Wg, bias, logits, idx, w, s);
+  else if (c.E <= 32) launch_gate_e<T, 2, 8>(c, x, Wg, bias, logits, idx, w, s);
+  else if (c.E <= 48) launch_gate_e<T, 3, 4>(c, x, Wg, bias, logits, idx, w, s);
+  else launch_gate_e<T, 4, 4>(c, x, Wg, bias, logits, idx, w, s);
 }
 
 void launch_gate(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
