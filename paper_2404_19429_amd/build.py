@@ -1,4 +1,4 @@
-"""Build liblancet_moe.so in-tree with hipcc for gfx950.
+"""Build liblancet_moe.so (hipcc, gfx950) and its Python binding _bind.so in-tree.
 
 Usage: python -m paper_2404_19429_amd.build [-v]
 Every source is compiled to an object under _build/ (in parallel), then
@@ -18,6 +18,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblancet_moe.so")
+BIND = os.path.join(PKG, "_bind.so")   # the native argument marshalling (a Python extension module)
 SOURCES = ["api.cpp", "block.cpp", "plan.cpp", "gate.hip", "route.hip", "gemm.hip", "gemm_256x256.hip",
            "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip", "norm.hip"]
 ARCH = "gfx950"
@@ -69,12 +70,33 @@ def _check_isa(src: str, verbose: bool) -> None:
         print(f"ISA check passed: {src}", flush=True)
 
 
+def _build_bind(verbose: bool) -> None:
+    """The Python extension that marshals arguments (host code against torch's headers)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           os.path.join(CSRC, "bind.cpp"), "-o", BIND + ".tmp", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"]]
+    for p in include_paths():
+        cmd += ["-isystem", p]
+    cmd += ["-L", tlib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on bind.cpp:\n" + r.stderr)
+    os.replace(BIND + ".tmp", BIND)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + len(ASM_READ_SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + len(ASM_READ_SOURCES) + 1)) as ex:
+        bind = ex.submit(_build_bind, verbose)
         isa = [ex.submit(_check_isa, s, verbose) for s in ASM_READ_SOURCES]
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        for f in isa:
+        for f in isa + [bind]:
             f.result()
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs

@@ -4,8 +4,9 @@ Argument marshalling only: every function here has the name of the C-ABI
 entry point it calls, checks that each tensor is a contiguous device tensor
 of the right dtype and at least the size the call will touch (the C ABI takes
 bare pointers and cannot check sizes), and passes pointers and the current
-HIP stream.  All computation happens in the HIP kernels.  There is no CPU
-fallback: if the library is missing, importing this module raises.
+HIP stream; the calls of a step do this in native code (csrc/bind.cpp).  All
+computation happens in the HIP kernels.  There is no CPU fallback: if the
+library or its binding is missing, importing this module raises.
 """
 from __future__ import annotations
 
@@ -117,6 +118,19 @@ def _load():
 _lib = _load()
 
 
+def _load_bind():
+    try:
+        from paper_2404_19429_amd import _bind
+    except ImportError as e:
+        raise ImportError("the native binding is not built; run `python -m paper_2404_19429_amd.build`") from e
+    _bind.init({n: ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in EXPORTS}, lambda s: _stream(s),
+               moe_cfg, moe_block_cfg)
+    return _bind
+
+
+_bind = _load_bind()
+
+
 # ----------------------------------------------------------------------- helpers
 def make_cfg(T, d_model, d_ff, E, k, C, G=1, dtype="bf16", act="gelu_tanh", renorm=1, wpacked=0,
              ksplit=1) -> moe_cfg:
@@ -141,26 +155,10 @@ def expert_numel(cfg: moe_cfg, X: int) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
-
-
-def _ptr(t: Optional[torch.Tensor], name: str, dtype, numel: int, nullable: bool = False):
-    if t is None:
-        if nullable:
-            return None
-        raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise ValueError(f"{name} must be a device tensor")
-    if t.dtype != dtype:
-        raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    if t.numel() < numel:
-        raise ValueError(f"{name} has {t.numel()} elements, the call touches {numel}")
-    return t.data_ptr() if t.numel() else None
 
 
 def _check(st: int):
@@ -182,46 +180,19 @@ def moe_last_error() -> str:
 
 
 def moe_gate_topk(cfg, x, Wg, bias, logits, idx, w, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, E, k = cfg.T, cfg.d_model, cfg.E, cfg.k
-    _check(_lib.moe_gate_topk(ctypes.byref(cfg), _ptr(x, "x", dt, T * d), _ptr(Wg, "Wg", dt, E * d),
-                              _ptr(bias, "bias", torch.float32, E, nullable=True),
-                              _ptr(logits, "logits", torch.float32, T * E), _ptr(idx, "idx", torch.int32, T * k),
-                              _ptr(w, "w", torch.float32, T * k), _stream(stream)))
+    _check(_bind.gate_topk(cfg, x, Wg, bias, logits, idx, w, stream))
 
 
 def moe_dispatch(cfg, x, idx, carry, fill, slot, send_buf, ws, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, E, k = cfg.T, cfg.d_model, cfg.E, cfg.k
-    need = moe_workspace_bytes(cfg, MOE_CALL_DISPATCH)
-    _check(_lib.moe_dispatch(ctypes.byref(cfg), _ptr(x, "x", dt, T * d), _ptr(idx, "idx", torch.int32, T * k),
-                             _ptr(carry, "carry", torch.int32, E, nullable=True), _ptr(fill, "fill", torch.int32, E),
-                             _ptr(slot, "slot", torch.int32, T * k), _ptr(send_buf, "send_buf", dt, expert_numel(cfg, d)),
-                             _ptr(ws, "ws", torch.uint8, need, nullable=need == 0),
-                             ws.numel() if ws is not None else 0, _stream(stream)))
+    _check(_bind.dispatch(cfg, x, idx, carry, fill, slot, send_buf, ws, stream))
 
 
 def moe_dispatch_noalloc(cfg, x, idx, carry, fill, slot, send_buf, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, E, k = cfg.T, cfg.d_model, cfg.E, cfg.k
-    _check(_lib.moe_dispatch_noalloc(ctypes.byref(cfg), _ptr(x, "x", dt, T * d), _ptr(idx, "idx", torch.int32, T * k),
-                                     _ptr(carry, "carry", torch.int32, E, nullable=True),
-                                     _ptr(fill, "fill", torch.int32, E), _ptr(slot, "slot", torch.int32, T * k),
-                                     _ptr(send_buf, "send_buf", dt, expert_numel(cfg, d)), _stream(stream)))
+    _check(_bind.dispatch_noalloc(cfg, x, idx, carry, fill, slot, send_buf, stream))
 
 
 def moe_dispatch_bpr(cfg, x, logits, idx, fill, slot, send_buf, order, ws, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, E, k = cfg.T, cfg.d_model, cfg.E, cfg.k
-    need = moe_workspace_bytes(cfg, MOE_CALL_DISPATCH_BPR)
-    _check(_lib.moe_dispatch_bpr(ctypes.byref(cfg), _ptr(x, "x", dt, T * d),
-                                 _ptr(logits, "logits", torch.float32, T * E), _ptr(idx, "idx", torch.int32, T * k),
-                                 _ptr(fill, "fill", torch.int32, E), _ptr(slot, "slot", torch.int32, T * k),
-                                 _ptr(send_buf, "send_buf", dt, expert_numel(cfg, d)),
-                                 _ptr(order, "order", torch.int32, T, nullable=True),
-                                 _ptr(ws, "ws", torch.uint8, need, nullable=need == 0),
-                                 ws.numel() if ws is not None else 0,
-                                 _stream(stream)))
+    _check(_bind.dispatch_bpr(cfg, x, logits, idx, fill, slot, send_buf, order, ws, stream))
 
 
 def moe_dw_schedule(kinds, times, edges):
@@ -275,67 +246,25 @@ def moe_pipeline_range_cost(kinds, times, join, i, n, k):
 
 
 def moe_pack_weights(cfg, W1, W2, W1p, W2p, stream=None):
-    dt = torch_dtype(cfg)
-    n = cfg.E * cfg.d_ff * cfg.d_model
-    _check(_lib.moe_pack_weights(ctypes.byref(cfg), _ptr(W1, "W1", dt, n), _ptr(W2, "W2", dt, n),
-                                 _ptr(W1p, "W1p", dt, n), _ptr(W2p, "W2p", dt, n), _stream(stream)))
+    _check(_bind.pack_weights(cfg, W1, W2, W1p, W2p, stream))
 
 
 def moe_expert_ffn_fwd(cfg, send_buf, row_begin, row_end, W1p, W2p, H, A, expert_out, ws=None, stream=None):
-    dt = torch_dtype(cfg)
-    d, f, E = cfg.d_model, cfg.d_ff, cfg.E
-    need = moe_workspace_bytes(cfg, MOE_CALL_FFN_FWD)
-    _check(_lib.moe_expert_ffn_fwd(ctypes.byref(cfg), _ptr(send_buf, "send_buf", dt, expert_numel(cfg, d)),
-                                   _ptr(row_begin, "row_begin", torch.int32, E, nullable=True),
-                                   _ptr(row_end, "row_end", torch.int32, E), _ptr(W1p, "W1p", dt, E * f * d),
-                                   _ptr(W2p, "W2p", dt, E * d * f), _ptr(H, "H", dt, expert_numel(cfg, f)),
-                                   _ptr(A, "A", dt, expert_numel(cfg, f)),
-                                   _ptr(expert_out, "expert_out", dt, expert_numel(cfg, d)),
-                                   _ptr(ws, "ws", torch.uint8, need, nullable=need == 0),
-                                   ws.numel() if ws is not None else 0, _stream(stream)))
+    _check(_bind.expert_ffn_fwd(cfg, send_buf, row_begin, row_end, W1p, W2p, H, A, expert_out, ws, stream))
 
 
 def moe_combine(cfg, expert_out, idx, slot, w, y, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, k = cfg.T, cfg.d_model, cfg.k
-    _check(_lib.moe_combine(ctypes.byref(cfg), _ptr(expert_out, "expert_out", dt, expert_numel(cfg, d)),
-                            _ptr(idx, "idx", torch.int32, T * k), _ptr(slot, "slot", torch.int32, T * k),
-                            _ptr(w, "w", torch.float32, T * k), _ptr(y, "y", dt, T * d), _stream(stream)))
+    _check(_bind.combine(cfg, expert_out, idx, slot, w, y, stream))
 
 
 def moe_bwd_dx(cfg, Wg, logits, idx, w, slot, row_begin, row_end, H, expert_out, W1p, W2p, dy, dO, dH, dXe,
                dlogits, dx, ws=None, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, f, E, k = cfg.T, cfg.d_model, cfg.d_ff, cfg.E, cfg.k
-    nd, nf = expert_numel(cfg, d), expert_numel(cfg, f)
-    need = moe_workspace_bytes(cfg, MOE_CALL_BWD_DX)
-    _check(_lib.moe_bwd_dx(ctypes.byref(cfg), _ptr(Wg, "Wg", dt, E * d), _ptr(logits, "logits", torch.float32, T * E),
-                           _ptr(idx, "idx", torch.int32, T * k), _ptr(w, "w", torch.float32, T * k),
-                           _ptr(slot, "slot", torch.int32, T * k),
-                           _ptr(row_begin, "row_begin", torch.int32, E, nullable=True),
-                           _ptr(row_end, "row_end", torch.int32, E), _ptr(H, "H", dt, nf),
-                           _ptr(expert_out, "expert_out", dt, nd), _ptr(W1p, "W1p", dt, E * f * d),
-                           _ptr(W2p, "W2p", dt, E * d * f), _ptr(dy, "dy", dt, T * d), _ptr(dO, "dO", dt, nd),
-                           _ptr(dH, "dH", dt, nf), _ptr(dXe, "dXe", dt, nd),
-                           _ptr(dlogits, "dlogits", torch.float32, T * E), _ptr(dx, "dx", dt, T * d),
-                           _ptr(ws, "ws", torch.uint8, need, nullable=need == 0),
-                           ws.numel() if ws is not None else 0, _stream(stream)))
+    _check(_bind.bwd_dx(cfg, Wg, logits, idx, w, slot, row_begin, row_end, H, expert_out, W1p, W2p, dy, dO, dH, dXe,
+                        dlogits, dx, ws, stream))
 
 
 def moe_bwd_dw(cfg, x, dlogits, row_begin, row_end, send_buf, A, dO, dH, dW1, dW2, dWg, ws, stream=None):
-    dt = torch_dtype(cfg)
-    T, d, f, E = cfg.T, cfg.d_model, cfg.d_ff, cfg.E
-    nd, nf = expert_numel(cfg, d), expert_numel(cfg, f)
-    need = moe_workspace_bytes(cfg, MOE_CALL_BWD_DW)
-    _check(_lib.moe_bwd_dw(ctypes.byref(cfg), _ptr(x, "x", dt, T * d, nullable=T == 0),
-                           _ptr(dlogits, "dlogits", torch.float32, T * E),
-                           _ptr(row_begin, "row_begin", torch.int32, E, nullable=True),
-                           _ptr(row_end, "row_end", torch.int32, E), _ptr(send_buf, "send_buf", dt, nd),
-                           _ptr(A, "A", dt, nf), _ptr(dO, "dO", dt, nd), _ptr(dH, "dH", dt, nf),
-                           _ptr(dW1, "dW1", dt, E * f * d), _ptr(dW2, "dW2", dt, E * d * f),
-                           _ptr(dWg, "dWg", torch.float32, E * d),
-                           _ptr(ws, "ws", torch.uint8, need, nullable=need == 0),
-                           ws.numel() if ws is not None else 0, _stream(stream)))
+    _check(_bind.bwd_dw(cfg, x, dlogits, row_begin, row_end, send_buf, A, dO, dH, dW1, dW2, dWg, ws, stream))
 
 
 # ------------------------------------------------------------- layer step driver
@@ -497,26 +426,7 @@ def moe_block_workspace_bytes(cfg: moe_block_cfg, n_chunks: int) -> int:
 def moe_block_chunked(cfg: moe_block_cfg, weights: dict, grads: Optional[dict], x, out, dy, dx, acts: dict,
                       passes: int, n_chunks: int, streams, ws):
     """streams: three torch.cuda.Stream (or raw handles) -- compute, data movement, weight gradients."""
-    shp = block_shapes(cfg, n_chunks)
-    T, d = cfg.moe.T, cfg.moe.d_model
-    bwd = bool(passes & MOE_BLOCK_BWD)
-    fwd = bool(passes & MOE_BLOCK_FWD)
-    w = moe_block_weights(*[_ptr(weights[n], n, shp[n][1], shp[n][0]) for n in BLOCK_WEIGHTS])
-    g = None
-    if bwd:
-        g = moe_block_grads(*[_ptr(grads[n], n, shp[n][1], shp[n][0]) for n in BLOCK_GRADS])
-    names = BLOCK_ACTS_FWD + (BLOCK_ACTS_BWD if bwd else [])
-    a = moe_block_acts(*[_ptr(acts[n], n, shp[n][1], shp[n][0]) if n in names else None
-                         for n in BLOCK_ACTS_FWD + BLOCK_ACTS_BWD])
-    need = moe_block_workspace_bytes(cfg, n_chunks)
-    st = (ctypes.c_void_p * 3)(*[_stream(s) for s in streams])
-    _check(_lib.moe_block_chunked(ctypes.byref(cfg), ctypes.byref(w), ctypes.byref(g) if g is not None else None,
-                                  _ptr(x, "x", torch.bfloat16, T * d),
-                                  _ptr(out, "out", torch.bfloat16, T * d) if fwd else None,
-                                  _ptr(dy, "dy", torch.bfloat16, T * d) if bwd else None,
-                                  _ptr(dx, "dx", torch.bfloat16, T * d) if bwd else None,
-                                  ctypes.byref(a), int(passes), int(n_chunks), st,
-                                  _ptr(ws, "ws", torch.uint8, need), ws.numel(), ))
+    _check(_bind.block_chunked(cfg, weights, grads, x, out, dy, dx, acts, passes, n_chunks, streams, ws))
 
 
 def alloc_block(cfg: moe_block_cfg, n_chunks: int, device="cuda", names=None) -> dict:
