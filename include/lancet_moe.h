@@ -406,7 +406,9 @@ size_t moe_block_workspace_bytes(const moe_block_cfg* cfg, int32_t n_chunks);
  *   streams[1] (data movement) runs partition i's dispatch as soon as its gate
  *   is done -- starting from the capacity partition i-1 left, so routing,
  *   slots and drops equal the unpartitioned layer -- and its combine (plus the
- *   residual h) as soon as its experts are done.  Partition i's dispatch thus
+ *   residual h) as soon as its experts are done (the last combine, and with
+ *   n_chunks = 1 the dispatch, overlap nothing: streams[0] runs them).
+ *   Partition i's dispatch thus
  *   overlaps partition i+1's attention, and its combine the next partition's
  *   experts.  The block's expert products never split a K sum (moe.ksplit
  *   is ignored and taken as 0), so every output is bitwise independent of
