@@ -20,7 +20,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblancet_moe.so")
 BIND = os.path.join(PKG, "_bind.so")   # the native argument marshalling (a Python extension module)
 SOURCES = ["api.cpp", "block.cpp", "plan.cpp", "gate.hip", "route.hip", "gemm.hip", "gemm_256x256.hip",
-           "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip", "norm.hip"]
+           "gemm_192x256.hip", "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip", "norm.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -51,7 +51,9 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-ASM_READ_SOURCES = ["gemm_256x256.hip", "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip", "attn.hip"]  # kernels that read LDS through inline asm
+# kernels that read LDS through inline asm
+ASM_READ_SOURCES = ["gemm_256x256.hip", "gemm_192x256.hip", "gemm_128x128.hip", "gemm_64x128.hip", "gemm_64x64.hip",
+                    "attn.hip"]
 
 
 def _check_isa(src: str, verbose: bool) -> None:

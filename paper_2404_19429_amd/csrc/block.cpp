@@ -219,7 +219,7 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       const int64_t t0 = Tc * i;
       if (Sd != Sc) HIP_TRY(hipStreamWaitEvent(Sc, ev_disp[i], 0));
       const int32_t* rb = i == 0 ? nullptr : A.fill + (int64_t)(i - 1) * E;
-      launch_expert_fwd(pc, A.send_buf, rb, A.fill + (int64_t)i * E, W1p, W2p, A.H, A.A, A.expert_out, wsb + L.sk, Sc);
+      launch_expert_fwd(pc, A.send_buf, rb, A.fill + (int64_t)i * E, W1p, W2p, A.H, A.A, A.expert_out, wsb + L.sk, Sc, i > 0);
       HIP_TRY(hipGetLastError());
       const hipStream_t Sy = i + 1 == n ? Sc : Sd;
       HIP_TRY(order(Sc, Sy));

@@ -242,24 +242,33 @@ size_t expert_sk_ws_bytes(const moe_cfg& c) { return c.dtype == MOE_BF16 ? (size
 // lies, 256-tiles against the choice: expert_out of 1531 tokens (d 768, f 3072,
 // 8 experts) 68 -> 26 us, of 48 tokens (d 1024, f 4096, 16 experts) 75 -> 44,
 // of 2048 tokens (d 768) 73 -> 40, of 3108 tokens 78 -> 65; at 4096 tokens
-// (d 1024, 16 experts) 110 stays against 128 with 128-tiles, and the fused
-// products keep 256-tiles from 2048 tokens on (37 against 41).
+// (d 1024, 16 experts) 128-tiles lose (128 against 110), and the fused products
+// keep 256-tiles from 2048 tokens on (37 against 41).  192-row tiles, for rows
+// that end just past a multiple of 256: expert_out of 4096 tokens (d 2048, 16
+// experts, no K-split) 372 -> 328, of 6000 tokens (d 1536, 32 experts) 178 -> 145;
+// of 16384 tokens (8 experts) 256-tiles stay, 948 against 971.
 struct TileCost {
   int bm, bn, slots;
   double full, part, store;
   void (*run)(const WideCall&, hipStream_t);
 };
 static const TileCost kTilesM[] = {{256, 256, 256, 650., 650., 8000., run_wide_256x256},
+                                   {192, 256, 256, 560., 560., 7000., run_wide_192x256},
                                    {128, 128, 512, 520., 330., 4500., run_wide_128x128},
                                    {64, 128, 512, 390., 230., 3000., run_wide_64x128},
                                    {64, 64, 512, 300., 190., 2000., run_wide_64x64}};
 static double tile_cost(const TileCost& t, const WideCall& w) {
-  // M-tiles of a group: the mean over one standard deviation of routed rows.
-  const double tm = 0.5 * (std::ceil(std::max(1., w.expect - w.spread) / t.bm) + std::ceil((w.expect + w.spread) / t.bm));
+  // M-tiles of a group: a mean over the routed rows' spread.
+  const double tm = 0.25 * std::ceil(std::max(1., w.expect - w.spread) / t.bm) + 0.5 * std::ceil(w.expect / t.bm) +
+                    0.25 * std::ceil((w.expect + w.spread) / t.bm);
   const double tiles = std::ceil(w.groups * tm * std::ceil((double)w.cols / t.bn));
   const double rounds = std::floor(tiles / t.slots), rem = tiles - rounds * t.slots;
   const double steps = w.p.K / 32., store = w.kind == WK_FWD1 || w.kind == WK_DACT ? t.store : t.store / 2;
-  return rounds * (steps * t.full + store) + (rem <= 0 ? 0. : steps * (rem <= 256 ? t.part : t.full) + store);
+  double last = rem <= 0 ? 0. : steps * (rem <= 256 ? t.part : t.full) + store;
+  // A K-split last round: its share of a round, and the partial tiles' write and sum.
+  if (t.bm == 256 && w.p.ksplit && (w.kind == WK_NK || w.kind == WK_KN) && rounds > 0 && rem > 0 && 4 * rem <= t.slots)
+    last = steps * t.full * rem / t.slots + 15000.;
+  return rounds * (steps * t.full + store) + last;
 }
 static void run_wide_any(const WideCall& w, hipStream_t s) {
   if (w.rows <= 0 || w.cols <= 0 || w.groups <= 0) return;
@@ -284,7 +293,8 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
 // rows: rows of the output per group (ragged-M: the capacity C, with up to 15
 // alignment rows; ragged-K: M); cols: N.
 template <bool B_K, bool RAGGED_K, int EPI>
-static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s) {
+static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s,
+                       bool later = false) {
   if (rows <= 0 || cols <= 0 || c.E <= 0) return;
   // Rows a group is expected to hold: the call's assignments spread evenly (T is
   // only a hint here: rows may come from elsewhere).
@@ -306,7 +316,8 @@ static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int
     else launch_f32<2, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
     return;
   }
-  run_wide_any(WideCall{kind, c.act, c.E, rows, cols, expect, spread, p}, s);
+  // A later partition's rows start anywhere in a 16-row block.
+  run_wide_any(WideCall{kind, c.act, c.E, rows, cols, expect + (later ? 7.5 : 0.), spread, p}, s);
 }
 
 // Rows per expert block of an [E][C][*] buffer (C rounded up to 16 for bf16).
@@ -400,19 +411,19 @@ hipError_t product_times(double* ms, int32_t* counts) {
 }
 
 void launch_expert_fwd(const moe_cfg& c, const void* X, const int32_t* rb, const int32_t* re, const void* W1,
-                       const void* W2, void* H, void* A, void* O, void* ws, hipStream_t s) {
+                       const void* W2, void* H, void* A, void* O, void* ws, hipStream_t s, bool later) {
   const int64_t d = c.d_model, f = c.d_ff, C = c.C, Cp = rows_alloc(c);
   GemmParams p1{X, d, Cp * d, W1, d, f * d, H, f, Cp * f, A, nullptr, rb, re, 0, (int)f, (int)d, c.act, (int)C};
   p1.part = (float*)ws;
   p1.ksplit = c.ksplit;
   bool tb = ptimer_begin(kProdFwd1, s);
-  run_expert<true, false, EPI_FWD1>(c, WK_FWD1, p1, C, (int)f, s);
+  run_expert<true, false, EPI_FWD1>(c, WK_FWD1, p1, C, (int)f, s, later);
   ptimer_end(tb, s);
   GemmParams p2{A, f, Cp * f, W2, f, d * f, O, d, Cp * d, nullptr, nullptr, rb, re, 0, (int)d, (int)f, c.act, (int)C};
   p2.part = (float*)ws;
   p2.ksplit = c.ksplit;
   tb = ptimer_begin(kProdFwd2, s);
-  run_expert<true, false, EPI_STORE>(c, WK_NK, p2, C, (int)d, s);   // expert_out row-major
+  run_expert<true, false, EPI_STORE>(c, WK_NK, p2, C, (int)d, s, later);   // expert_out row-major
   ptimer_end(tb, s);
 }
 

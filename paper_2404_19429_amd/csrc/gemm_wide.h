@@ -128,17 +128,18 @@ constexpr int kPanelN = 8;
 // waves per SIMD, and whether a short last round may be K-split.  A product
 // sums the same 32-wide MFMAs in K order whatever its tile, so tiles of any
 // shape give the same bits.
-template <int BM_, int BN_, int NW_, int WGN_, int SUB_, int STB, int STT, int WPE_, bool KSPLIT_>
+template <int BM_, int BN_, int NW_, int WGN_, int SUB_, int STB, int STT, int WPE_, bool KSPLIT_, int BMT_ = BM_>
 struct Wide {
   static constexpr int BM = BM_, BN = BN_, NW = NW_, WGN = WGN_, SUB = SUB_;
   static constexpr int BK = 32 * SUB;                     // K per step: SUB MFMA K-steps of 32
   static constexpr int WGM = NW / WGN;                    // wave grid WGM x WGN
-  static constexpr int WTM = BM / WGM, WTN = BN / WGN;    // wave tile
+  static constexpr int BMT = BMT_;                        // rows of a tile (the LDS stage has room for BM)
+  static constexpr int WTM = BMT / WGM, WTN = BN / WGN;   // wave tile
   static constexpr int FM = WTM / 16, FN = WTN / 16;      // fragments per wave tile side
   static constexpr int NIA = BM / 16 / NW, NIB = BN / 16 / NW;   // loads per wave and 32 K (1 KB each)
   static constexpr int HALF = (BM + BN) * kBKb;           // elements per 32 K: A tile, then B tile
   static constexpr int STAGE = SUB * HALF;                // elements per pipeline stage
-  static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0 && WTM % 32 == 0 && WTN % 32 == 0, "tile / waves mismatch");
+  static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0 && WTM % 32 == 0 && WTN % 32 == 0 && BMT <= BM, "tile / waves mismatch");
   static constexpr int WPE = WPE_;                        // waves per SIMD
   static constexpr int stages(bool b_k) { return b_k ? STB : STT; }
   static constexpr bool pair(bool b_k) { return stages(b_k) >= 5; }
@@ -458,7 +459,7 @@ __device__ __forceinline__ void wide_epilogue(const GemmParams& p, const WGeo& G
     const int64_t e = CBLK ? blk_off((RAGGED_K ? 0 : G.lo_al) + row, col, p.ldc) : (int64_t)row * p.ldc + col;
     return ok ? (uint32_t)(e * ESZ) : kOob;
   };
-  constexpr int HR = FM < 4 ? FM : 4;
+  constexpr int HR = FM % 4 == 0 ? 4 : FM % 3 == 0 ? 3 : 2;
 #pragma unroll
   for (int h = 0; h < FM / HR; ++h) {    // groups of up to four fragment rows
     u32x2 aux[HR][FN];
@@ -520,7 +521,7 @@ template <class TC, bool B_K, bool RAGGED_K, int EPI, int ACT, bool CBLK>
 __global__ __attribute__((amdgpu_flat_work_group_size(TC::NW * 64, TC::NW * 64), amdgpu_waves_per_eu(TC::WPE, TC::WPE))) void
 gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   constexpr int BK = TC::BK, SUB = TC::SUB, HALF = TC::HALF;
-  constexpr int BM = TC::BM, BN = TC::BN, NW = TC::NW, WGN = TC::WGN;
+  constexpr int BM = TC::BM, BN = TC::BN, BMT = TC::BMT, NW = TC::NW, WGN = TC::WGN;
   constexpr int WTM = TC::WTM, WTN = TC::WTN;   // wave tile
   constexpr int FM = TC::FM, FN = TC::FN;       // fragments per wave tile side
   constexpr int NIA = TC::NIA, NIB = TC::NIB;
@@ -533,6 +534,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // size past its end would wrap): ragged-M products have K a multiple of 64,
   // a ragged-K group may end in any 32 rows.
   static_assert(SUB == 1 || (SUB == 2 && !RAGGED_K), "two halves per step: ragged-M products only");
+  static_assert(BMT == BM || !RAGGED_K, "short tiles: ragged-M products only");
   static_assert(STAGES >= 2 && LPS * (STAGES - 1) < 64, "vmcnt range");
   constexpr bool PAIR = TC::pair(B_K);
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
@@ -548,7 +550,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // The K-split products place their short tiles last (SEP), so the split
   // round holds the short tiles, whose partial sums stop at the group's rows.
   constexpr bool SPLIT = TC::KSPLIT && !RAGGED_K && EPI == EPI_STORE;
-  const WPrefix P = wide_tile_prefix<BM, RAGGED_K, SPLIT>(p, lane, groups, tilesM, tilesN);
+  const WPrefix P = wide_tile_prefix<BMT, RAGGED_K, SPLIT>(p, lane, groups, tilesM, tilesN);
   const int total = P.NF + P.NP;
   if constexpr (RAGGED_K) {
     // Groups without rows have no tiles: their [M][N] outputs are zeroed here,
@@ -593,7 +595,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   if (nseg == 0) return;
 
   auto geo = [&](int t) __attribute__((always_inline)) {
-    return wide_geo<BM, BN, BK, RAGGED_K, SPLIT>(p, t, lane, groups, P, tilesM, tilesN);
+    return wide_geo<BMT, BN, BK, RAGGED_K, SPLIT>(p, t, lane, groups, P, tilesM, tilesN);
   };
 
   // Segment e: tile, first K-step, end K-step (0 = the tile's own count).
@@ -622,7 +624,9 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
     const uint16_t* Ab = (const uint16_t*)p.A + (RMO ? 0 : G.g * p.sA);
     const uint16_t* Bb = (const uint16_t*)p.B + (RMO ? 0 : G.g * p.sB);
     const int64_t extA = RMO ? (int64_t)p.cap * p.lda : p.sA, extB = RMO ? (int64_t)p.cap * p.ldb : p.sB;
-    if constexpr (AK) opA.plan(Ab, p.sA, p.lda, G.lo_al + G.m0, (int)pad16(p.cap), 0, 0, 0, wid, lane);
+    // (rows of the stage past the tile's BMT are not loaded: their places get zeros, which no wave reads)
+    const int rlim = min((int)pad16(p.cap), G.lo_al + G.m0 + BMT);
+    if constexpr (AK) opA.plan(Ab, p.sA, p.lda, G.lo_al + G.m0, rlim, 0, 0, 0, wid, lane);
     else opA.plan(Ab, extA, p.lda, G.m0, p.M, G.lo_al, G.lo, G.hi, wid, lane);
     if constexpr (BKK) opB.plan(Bb, p.sB, p.ldb, G.n0, p.N, 0, 0, 0, wid, lane);
     else if constexpr (RAGGED_K) opB.plan(Bb, extB, p.ldb, G.n0, p.N, G.lo_al, G.lo, G.hi, wid, lane);
@@ -898,7 +902,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // reads them).
   auto partial = [&](const WGeo& Cg) __attribute__((always_inline)) {
     asm volatile("s_nop 15\n s_nop 15" ::: "memory");   // last MFMA -> accumulator reads
-    float* mine = p.part + (int64_t)blockIdx.x * (BM * BN) + ((int64_t)wid * FM * FN * 64 + lane) * 4;
+    float* mine = p.part + (int64_t)blockIdx.x * (BMT * BN) + ((int64_t)wid * FM * FN * 64 + lane) * 4;
     const int rows = Cg.Mlim - (Cg.m0 + wm * WTM);   // the wave's rows in the group (uniform)
     // One fragment row at a time (the pin orders each row's register moves
     // after the previous row's stores, so only a row is ever out of AGPRs).
@@ -961,7 +965,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
 template <class TC, int EPI, int ACT, bool CBLK>
 __global__ __launch_bounds__(TC::NW * 64) void gemm_wide_fixup_kernel(GemmParams p, int tilesM, int tilesN, int groups,
                                                                    int nslot) {
-  constexpr int BM = TC::BM, BN = TC::BN, WGN = TC::WGN, WTM = TC::WTM, WTN = TC::WTN, FM = TC::FM, FN = TC::FN;
+  constexpr int BM = TC::BMT, BN = TC::BN, WGN = TC::WGN, WTM = TC::WTM, WTN = TC::WTN, FM = TC::FM, FN = TC::FN;
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wid / WGN, wn = wid % WGN;
@@ -1041,9 +1045,9 @@ static void launch_wide(const WideCall& w, hipStream_t s) {
   auto kern = gemm_wide_kernel<TC, B_K, RAGGED_K, EPI, ACT, CBLK>;
   static std::atomic<uint64_t> lds_ok{0};
   allow_dyn_lds((const void*)kern, (int)shmem, lds_ok);
-  const int tm = (int)((w.rows + (RAGGED_K ? 0 : 15) + TC::BM - 1) / TC::BM), tn = (w.cols + TC::BN - 1) / TC::BN;
+  const int tm = (int)((w.rows + (RAGGED_K ? 0 : 15) + TC::BMT - 1) / TC::BMT), tn = (w.cols + TC::BN - 1) / TC::BN;
   int64_t blocks = (int64_t)num_cus() * TC::per_cu(B_K);
-  if (SPLIT) blocks = std::min<int64_t>(blocks, kSkPartElems / (TC::BM * TC::BN));   // partial tiles in the workspace
+  if (SPLIT) blocks = std::min<int64_t>(blocks, kSkPartElems / (TC::BMT * TC::BN));   // partial tiles in the workspace
   blocks = std::min(blocks, (int64_t)tm * tn * w.groups);
   blocks = (blocks + 7) / 8 * 8;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TC::NW * 64), shmem, s, p, tm, tn, w.groups);
@@ -1091,6 +1095,7 @@ static void run_wide_k(const WideCall& w, hipStream_t s) {
 
 // One source file per tile shape (they compile in parallel).
 void run_wide_256x256(const WideCall& w, hipStream_t s);
+void run_wide_192x256(const WideCall& w, hipStream_t s);  // ragged-M products only
 void run_wide_128x128(const WideCall& w, hipStream_t s);
 void run_wide_64x128(const WideCall& w, hipStream_t s);   // ragged-M products only
 void run_wide_64x64(const WideCall& w, hipStream_t s);    // ragged-M products only

@@ -90,9 +90,10 @@ void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void*
 // gemm.hip: expert GEMMs over [E][C][*] buffers with per-expert row ranges.
 // The row-ragged products take a workspace of expert_sk_ws_bytes(c) bytes
 // (partial tiles and counters of their K-split schedule; unused for float).
+// later: a batch partition after the first (a hint for the tile choice).
 size_t expert_sk_ws_bytes(const moe_cfg& c);
 void launch_expert_fwd(const moe_cfg& c, const void* X, const int32_t* rb, const int32_t* re, const void* W1,
-                       const void* W2, void* H, void* A, void* O, void* ws, hipStream_t s);
+                       const void* W2, void* H, void* A, void* O, void* ws, hipStream_t s, bool later = false);
 void launch_expert_bwd_dx(const moe_cfg& c, const void* dO, const int32_t* rb, const int32_t* re, const void* H,
                           const void* W1, const void* W2, void* dH, void* dXe, void* ws, hipStream_t s);
 void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const void* dO, const void* dH,

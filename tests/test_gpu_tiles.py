@@ -42,6 +42,8 @@ CASES = {
     "rows_258_129_86_edges": (_s(258, 128, 832, 2, 2), 3),
     "skewed": (_s(1536, 128, 1024, 16, 2, zipf_s=1.2, cf_num=1, cf_den=1), 4),
     "large_then_small": (_s(4096, 64, 2048, 8, 2, act="relu"), 32),
+    # 8 experts x 270 rows: the whole batch on 192-row tiles, half of it on 128-row ones
+    "rows_270_135": (_s(270, 768, 3200, 8, 8), 2),
 }
 
 
