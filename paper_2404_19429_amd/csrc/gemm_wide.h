@@ -454,64 +454,94 @@ __device__ __forceinline__ void wide_epilogue(const GemmParams& p, const WGeo& G
     rC2 = __builtin_amdgcn_make_buffer_rsrc((uint16_t*)p.C2 + cofs, (short)0, 0x7fffffff, kBufCfg);
   if constexpr (EPI == EPI_DACT || EPI == EPI_RES)
     rAux = __builtin_amdgcn_make_buffer_rsrc((uint16_t*)p.Aux + cofs, (short)0, 0x7fffffff, kBufCfg);
-  const int rl = lane & 15, cq = 4 * (lane >> 4);
+  const int rl = lane & 15, q = lane >> 4;
   auto voff = [&](bool ok, int row, int col) __attribute__((always_inline)) -> uint32_t {
     const int64_t e = CBLK ? blk_off((RAGGED_K ? 0 : G.lo_al) + row, col, p.ldc) : (int64_t)row * p.ldc + col;
     return ok ? (uint32_t)(e * ESZ) : kOob;
   };
+  auto row_of = [&](int i) __attribute__((always_inline)) { return G.m0 + wm * WTM + 16 * i + rl; };
+  auto row_ok = [&](int i) __attribute__((always_inline)) {
+    const int row = row_of(i);
+    return row < G.Mlim && (RAGGED_K || G.lo_al + row >= G.lo) && i >= i_lo && i < i_hi;
+  };
+  if constexpr (EPI == EPI_WGF32) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int col = G.n0 + wn * WTN + 16 * j + 4 * q;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), rC,
+                                               (int)voff(row_ok(i) && col < p.N, row_of(i), col), 0, 0);
+      }
+    return;
+  }
+  // bf16 outputs move as 16 bytes per lane: of a pair of fragments (32 columns)
+  // a lane holds columns 4 q .. +3 of each 16; swapping the odd 16-lane groups of
+  // the first with the even ones of the second leaves it columns cq .. cq + 7 of
+  // the 32, cq = 16 (q % 2) + 8 (q / 2), so a wave's store covers whole 64-byte
+  // row pieces (a blocked output: one contiguous KiB) with half the instructions.
+  const int cq = 16 * (q & 1) + 8 * (q >> 1);
+  constexpr int FP = FN / 2;
+  auto swap = [](u32x2& a, u32x2& b) __attribute__((always_inline)) {   // (its own inverse)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const auto r = __builtin_amdgcn_permlane16_swap(a[u], b[u], false, false);
+      a[u] = r[0];
+      b[u] = r[1];
+    }
+  };
+  auto store = [&](u32x2 a, u32x2 b, __amdgpu_buffer_rsrc_t rs, int vo) __attribute__((always_inline)) {
+    swap(a, b);
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{a[0], a[1], b[0], b[1]}, rs, vo, 0, 0);
+  };
   constexpr int HR = FM % 4 == 0 ? 4 : FM % 3 == 0 ? 3 : 2;
 #pragma unroll
   for (int h = 0; h < FM / HR; ++h) {    // groups of up to four fragment rows
-    u32x2 aux[HR][FN];
-    if constexpr (EPI == EPI_DACT || EPI == EPI_RES) {   // all loads of the half first, then the math
+    u32x4 aux[HR][FP];
+    if constexpr (EPI == EPI_DACT || EPI == EPI_RES) {   // all loads of the group first, then the math
 #pragma unroll
-      for (int ii = 0; ii < HR; ++ii) {
-        const int row = G.m0 + wm * WTM + 16 * (HR * h + ii) + rl;
-        const bool rok = row < G.Mlim && (RAGGED_K || G.lo_al + row >= G.lo) && HR * h + ii >= i_lo && HR * h + ii < i_hi;
+      for (int ii = 0; ii < HR; ++ii)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int col = G.n0 + wn * WTN + 16 * j + cq;
-          aux[ii][j] = __builtin_amdgcn_raw_buffer_load_b64(rAux, (int)voff(rok && col < p.N, row, col), 0, 0);
+        for (int jp = 0; jp < FP; ++jp) {
+          const int col = G.n0 + wn * WTN + 32 * jp + cq;
+          aux[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(
+              rAux, (int)voff(row_ok(HR * h + ii) && col < p.N, row_of(HR * h + ii), col), 0, 0);
         }
-      }
     }
 #pragma unroll
     for (int ii = 0; ii < HR; ++ii) {
       const int i = HR * h + ii;
       if (i < i_lo || i >= i_hi) continue;
-      const int row = G.m0 + wm * WTM + 16 * i + rl;
-      const bool rok = row < G.Mlim && (RAGGED_K || G.lo_al + row >= G.lo);
 #pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int col = G.n0 + wn * WTN + 16 * j + cq;
-        const int vo = (int)voff(rok && col < p.N, row, col);
-        float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      for (int jp = 0; jp < FP; ++jp) {
+        const int col = G.n0 + wn * WTN + 32 * jp + cq;
+        const int vo = (int)voff(row_ok(i) && col < p.N, row_of(i), col);
+        float v[2][4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[e][u] = acc[i][2 * jp + e][u];
         if constexpr (EPI == EPI_FWD1) {
-          __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rC, vo, 0, 0);
+          store(pack4_bf16(v[0]), pack4_bf16(v[1]), rC, vo);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = act_fwd_t<ACT>(v[u]);
-          __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rC2, vo, 0, 0);
-        } else if constexpr (EPI == EPI_DACT) {
-          const u32x2 hv = aux[ii][j];
-          const float hh[4] = {__uint_as_float(hv[0] << 16), __uint_as_float(hv[0] & 0xffff0000u),
-                               __uint_as_float(hv[1] << 16), __uint_as_float(hv[1] & 0xffff0000u)};
+          for (int e = 0; e < 2; ++e)
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] *= act_bwd_t<ACT>(hh[u]);
-          __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rC, vo, 0, 0);
-        } else if constexpr (EPI == EPI_WGF32) {
-          __builtin_amdgcn_raw_buffer_store_b128(
-              u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, rC, vo,
-              0, 0);
-        } else if constexpr (EPI == EPI_RES) {
-          const u32x2 rv = aux[ii][j];
-          v[0] += __uint_as_float(rv[0] << 16);
-          v[1] += __uint_as_float(rv[0] & 0xffff0000u);
-          v[2] += __uint_as_float(rv[1] << 16);
-          v[3] += __uint_as_float(rv[1] & 0xffff0000u);
-          __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rC, vo, 0, 0);
-        } else {
-          __builtin_amdgcn_raw_buffer_store_b64(pack4_bf16(v), rC, vo, 0, 0);
+            for (int u = 0; u < 4; ++u) v[e][u] = act_fwd_t<ACT>(v[e][u]);
+          store(pack4_bf16(v[0]), pack4_bf16(v[1]), rC2, vo);
+          continue;
         }
+        if constexpr (EPI == EPI_DACT || EPI == EPI_RES) {
+          u32x2 x[2] = {u32x2{aux[ii][jp][0], aux[ii][jp][1]}, u32x2{aux[ii][jp][2], aux[ii][jp][3]}};
+          swap(x[0], x[1]);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float f[4] = {__uint_as_float(x[e][0] << 16), __uint_as_float(x[e][0] & 0xffff0000u),
+                                __uint_as_float(x[e][1] << 16), __uint_as_float(x[e][1] & 0xffff0000u)};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[e][u] = EPI == EPI_DACT ? v[e][u] * act_bwd_t<ACT>(f[u]) : v[e][u] + f[u];
+          }
+        }
+        store(pack4_bf16(v[0]), pack4_bf16(v[1]), rC, vo);
       }
     }
   }
