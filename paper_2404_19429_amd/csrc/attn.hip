@@ -146,17 +146,17 @@ __device__ __forceinline__ void store4(uint16_t* p, float a, float b, float c, f
 }
 
 // ------------------------------------------------------------------- forward
-// Block: 4 waves x 32 queries = 128 queries of one (sequence, head); key tiles
-// of 64 up to the block's last query.  Grid: q tiles, heaviest (last) first,
+// Block: 4 waves x 16 NF queries of one (sequence, head), NF = 2 (128 queries) or
+// 1; key tiles of 64 up to the block's last query.  Grid: q tiles, heaviest (last) first,
 // times sequences x heads (so all q tiles of one head share an XCD's L2).
-constexpr int kFwdQ = 128;
-
+template <int NF>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2))) void
 attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint16_t* __restrict__ o_blk,
                 float* __restrict__ lse, int S, int Sp, int H, int nbh, float c2) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[2][2][kTileElems];  // [stage][K, V]
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int g = lane >> 4, jq = lane & 15;
+  constexpr int kFwdQ = 64 * NF;
   const int nqt = (S + kFwdQ - 1) / kFwdQ;
   const int qt = nqt - 1 - (int)(blockIdx.x / nbh);
   const int bh = (int)(blockIdx.x % nbh);
@@ -167,7 +167,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
   const uint16_t* Kb = Qb + d;
   const uint16_t* Vb = Qb + 2 * d;
   const int q0 = qt * kFwdQ;
-  const int qw = q0 + 32 * wid;              // this wave's first query
+  const int qw = q0 + 16 * NF * wid;         // this wave's first query
   const int kend = min(S, q0 + kFwdQ);
   const int nkt = (kend + kTR - 1) / kTR;
 
@@ -176,29 +176,36 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
     load_tile<4>(Vb, ld, kt * kTR, S, lds[kt & 1][1], wid, lane);
   };
   // Q as the B operand of S^T = K Q^T: query qw + 16 qf + l%16, columns 32 kk + 8 g.
-  u32x4 qf[2][4];
+  u32x4 qf[NF][4];
 #pragma unroll
-  for (int f = 0; f < 2; ++f)
+  for (int f = 0; f < NF; ++f)
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qf[f][kk] = load_row16(Qb, ld, qw + 16 * f + jq, S, 32 * kk + 8 * g);
   issue(0);
 
-  f32x4 acc_o[8][2];
+  f32x4 acc_o[8][NF];
+  float mrow[NF], lsum[NF];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc_o[i][0] = acc_o[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float mrow[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
+  for (int f = 0; f < NF; ++f) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc_o[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mrow[f] = -INFINITY;
+    lsum[f] = 0.f;
+  }
 
   for (int kt = 0; kt < nkt; ++kt) {
     wait_vm<0>();
     lds_barrier();  // tile kt is in LDS; every wave is done with tile kt-1's stage
     if (kt + 1 < nkt) issue(kt + 1);
     const int k0 = kt * kTR;
-    if (k0 > qw + 31) continue;  // every key of this tile is after every query of this wave
+    if (k0 > qw + 16 * NF - 1) continue;  // every key of this tile is after every query of this wave
     const uint16_t* Ks = lds[kt & 1][0];
     const uint16_t* Vs = lds[kt & 1][1];
-    f32x4 s[4][2];
+    f32x4 s[4][NF];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[i][0] = s[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) s[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
     // Reads one batch ahead of the MFMAs: K columns 0..63 (wait), then K
     // columns 64..127 in flight under the first half's MFMAs, then the first V
     // batch in flight under the second half's MFMAs and the softmax.
@@ -211,7 +218,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
 #pragma unroll
     for (int u = 0; u < 8; ++u)
 #pragma unroll
-      for (int f = 0; f < 2; ++f) s[u % 4][f] = mfma(kf0[u], qf[f][u / 4], s[u % 4][f]);
+      for (int f = 0; f < NF; ++f) s[u % 4][f] = mfma(kf0[u], qf[f][u / 4], s[u % 4][f]);
     __builtin_amdgcn_sched_barrier(0);
     lds_wait(kf1);
     cols_issue(vp, Vs, 0, lane);
@@ -219,17 +226,17 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
 #pragma unroll
     for (int u = 0; u < 8; ++u)
 #pragma unroll
-      for (int f = 0; f < 2; ++f) s[u % 4][f] = mfma(kf1[u], qf[f][2 + u / 4], s[u % 4][f]);
+      for (int f = 0; f < NF; ++f) s[u % 4][f] = mfma(kf1[u], qf[f][2 + u / 4], s[u % 4][f]);
     __builtin_amdgcn_sched_barrier(0);
     // Online softmax per query (lane column); keys 16 i + 4 g + v.  The
     // running max is kept in the base-2 units of s c2 (c2 > 0, and rounding is
     // monotonic, so the max of the products is the product of the max), and
     // p = 2^(s c2 - m) is one fused multiply-add ahead of the exponential.
     // Only a tile reaching past the wave's first query has keys to mask.
-    u32x4 pb[2][2];
+    u32x4 pb[NF][2];
     const bool diag = k0 + kTR - 1 > qw;
 #pragma unroll
-    for (int f = 0; f < 2; ++f) {
+    for (int f = 0; f < NF; ++f) {
       const int q = qw + 16 * f + jq;
       if (diag) {
 #pragma unroll
@@ -273,7 +280,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < NF; ++f)
           acc_o[2 * c + (u >> 1)][f] = mfma(vf[u], pb[f][u & 1], acc_o[2 * c + (u >> 1)][f]);
       __builtin_amdgcn_sched_barrier(0);
       if (c + 1 < 4) cols_finish(vf, vp);
@@ -283,7 +290,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ o, uint
   // Normalise and store: lane holds query qw + 16 f + l%16, head columns 16 i + 4 g .. +3.
   uint16_t* Ob = o + (int64_t)b * S * d + h * kHD;
 #pragma unroll
-  for (int f = 0; f < 2; ++f) {
+  for (int f = 0; f < NF; ++f) {
     const float l = group_sum(lsum[f]);
     const int q = qw + 16 * f + jq;
     if (q < S) {
@@ -639,10 +646,16 @@ attn_dkdv_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ 
 void launch_attn_fwd(const void* qkv, void* o, float* lse, int nseq, int S, int H, hipStream_t s, void* o_blk) {
   if (nseq <= 0 || S <= 0) return;
   const int nbh = nseq * H;
-  const int nqt = (S + kFwdQ - 1) / kFwdQ;
   const float c2 = kLog2e / sqrtf((float)kHD);
-  hipLaunchKernelGGL(attn_fwd_kernel, dim3((unsigned)(nqt * nbh)), dim3(256), 0, s, (const uint16_t*)qkv,
-                     (uint16_t*)o, (uint16_t*)o_blk, lse, S, attn_stat_stride(S), H, nbh, c2);
+  auto go = [&](auto kern, int q) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((S + q - 1) / q * nbh)), dim3(256), 0, s, (const uint16_t*)qkv,
+                       (uint16_t*)o, (uint16_t*)o_blk, lse, S, attn_stat_stride(S), H, nbh, c2);
+  };
+  // 64 queries per block where 128 would not give every CU its two blocks: a
+  // wave's chain per key tile is then half as long, on twice the CUs (500 tokens x 8
+  // heads 18.8 -> 14.1 us; 2 x 777 tokens x 6 heads 27 -> 21).
+  if ((int64_t)((S + 127) / 128) * nbh < 2 * num_cus()) go(attn_fwd_kernel<1>, 64);
+  else go(attn_fwd_kernel<2>, 128);
 }
 
 void launch_attn_bwd(const void* qkv, const void* o, const void* dout, const float* lse, float* delta, void* dqkv,
