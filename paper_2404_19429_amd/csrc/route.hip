@@ -32,44 +32,24 @@ __device__ __forceinline__ int64_t erow(int e, int s, int col, int d, int C) {
 }
 
 // ------------------------------------------------------------ slot assignment
-// For every assignment (t, r) of a chunk: rank[t][r] = assignments to the same
-// expert earlier in (token, rank) order inside the chunk; counts[chunk][e] =
-// the chunk's assignments to e.  Lanes holding the same expert are found with
-// one ballot per expert-index bit.
-// perm (nullable): position j of the walk holds token perm[j] (batch-prioritized
-// order); NULL = token order.  rank_out and the chunks are indexed by position.
-__global__ __launch_bounds__(kRouteChunk) void route_rank_kernel(const int32_t* __restrict__ idx,
-                                                                 const int32_t* __restrict__ perm,
-                                                                 int32_t* __restrict__ counts,
-                                                                 int32_t* __restrict__ rank_out,
-                                                                 int64_t T_tokens, int E, int k) {
-  constexpr int NW = kRouteChunk / kWave;
-  __shared__ int32_t wcnt[NW][kMaxE];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < NW * kMaxE; i += blockDim.x) (&wcnt[0][0])[i] = 0;
+// Ranks of a chunk's assignments, one thread per token with choices my[0 .. k-1]
+// (-1: none): rank[r] = assignments to the same expert earlier in (token, rank)
+// order inside the chunk; wcnt[w][e] = wave w's assignments to e (complete when
+// the call returns).  Lanes holding the same expert are found with one ballot
+// per expert-index bit.  Every thread of the block calls it.
+constexpr int kRouteWaves = kRouteChunk / kWave;
+__device__ __forceinline__ void chunk_ranks(const int (&my)[kMaxK], int k, int (&rank)[kMaxK],
+                                            int32_t (&wcnt)[kRouteWaves][kMaxE]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < kRouteWaves * kMaxE; i += kRouteChunk) (&wcnt[0][0])[i] = 0;
   __syncthreads();
-
-  const int64_t t = (int64_t)blockIdx.x * kRouteChunk + threadIdx.x;
-  const bool active = t < T_tokens;
-  int64_t tok = t;
-  if (active && perm) {
-    tok = perm[t];
-    if (tok < 0 || tok >= T_tokens) tok = t;   // (a valid order is a permutation of 0 .. T-1)
-  }
-  int my[kMaxK], rank[kMaxK];
-#pragma unroll
-  for (int r = 0; r < kMaxK; ++r) {
-    const int e = (active && r < k) ? idx[tok * k + r] : -1;
-    my[r] = (e >= 0 && e < E) ? e : -1;  // an out-of-range expert is treated as dropped
-    rank[r] = 0;
-  }
   // Earlier choices of the same token (only if a row repeats an expert).
 #pragma unroll
-  for (int r = 1; r < kMaxK; ++r)
+  for (int r = 0; r < kMaxK; ++r) {
+    rank[r] = 0;
 #pragma unroll
     for (int q = 0; q < r; ++q) rank[r] += (my[r] >= 0 && my[q] == my[r]) ? 1 : 0;
-
+  }
   // Round rp: the bit masks of every lane's rp-th choice let each lane count,
   // for each of its own choices, the lower lanes whose rp-th choice matches.
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -96,24 +76,104 @@ __global__ __launch_bounds__(kRouteChunk) void route_rank_kernel(const int32_t* 
     }
   }
   __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kMaxK; ++r)
+    if (r < k && my[r] >= 0)
+      for (int w = 0; w < wave; ++w) rank[r] += wcnt[w][my[r]];
+}
+// The choices of walk position t (token perm[t], or t), for chunk_ranks; returns the token.
+__device__ __forceinline__ int64_t walk_choices(const int32_t* idx, const int32_t* perm, int64_t t, int64_t T_tokens,
+                                                int E, int k, int (&my)[kMaxK]) {
+  const bool active = t < T_tokens;
+  int64_t tok = t;
+  if (active && perm) {
+    tok = perm[t];
+    if (tok < 0 || tok >= T_tokens) tok = t;   // (a valid order is a permutation of 0 .. T-1)
+  }
+#pragma unroll
+  for (int r = 0; r < kMaxK; ++r) {
+    const int e = (active && r < k) ? idx[tok * k + r] : -1;
+    my[r] = (e >= 0 && e < E) ? e : -1;  // an out-of-range expert is treated as dropped
+  }
+  return tok;
+}
+
+// counts[chunk][e] = the chunk's assignments to e; rank_out[t][r] as chunk_ranks (-1: none).
+// perm (nullable): position j of the walk holds token perm[j] (batch-prioritized
+// order); NULL = token order.  rank_out and the chunks are indexed by position.
+__global__ __launch_bounds__(kRouteChunk) void route_rank_kernel(const int32_t* __restrict__ idx,
+                                                                 const int32_t* __restrict__ perm,
+                                                                 int32_t* __restrict__ counts,
+                                                                 int32_t* __restrict__ rank_out,
+                                                                 int64_t T_tokens, int E, int k) {
+  __shared__ int32_t wcnt[kRouteWaves][kMaxE];
+  const int64_t t = (int64_t)blockIdx.x * kRouteChunk + threadIdx.x;
+  int my[kMaxK], rank[kMaxK];
+  walk_choices(idx, perm, t, T_tokens, E, k, my);
+  chunk_ranks(my, k, rank, wcnt);
   for (int e = threadIdx.x; e < E; e += blockDim.x) {
     int n = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) n += wcnt[w][e];
+    for (int w = 0; w < kRouteWaves; ++w) n += wcnt[w][e];
     counts[(int64_t)blockIdx.x * E + e] = n;
   }
-  if (!active) return;
+  if (t >= T_tokens) return;
+#pragma unroll
+  for (int r = 0; r < kMaxK; ++r)
+    if (r < k) rank_out[t * k + r] = my[r] >= 0 ? rank[r] : -1;
+}
+
+// The whole dispatch of at most one chunk of tokens in one launch: every block
+// ranks the chunk by itself (a microsecond beside a launch and its wait) and
+// copies its share of the 16-byte pieces; block 0 writes slot and fill.
+template <typename T>
+__global__ __launch_bounds__(kRouteChunk) void dispatch_small_kernel(const T* __restrict__ x,
+                                                                     const int32_t* __restrict__ idx,
+                                                                     const int32_t* __restrict__ perm,
+                                                                     const int32_t* __restrict__ carry,
+                                                                     int32_t* __restrict__ fill,
+                                                                     int32_t* __restrict__ slot, T* __restrict__ send,
+                                                                     int n, int d, int E, int k, int C) {
+  constexpr int V = Vec<T>::N;
+  __shared__ int32_t wcnt[kRouteWaves][kMaxE];
+  __shared__ int32_t tok_of[kRouteChunk];
+  __shared__ int32_t row[kRouteChunk * kMaxK];          // slot of (position, choice), -1: none
+  __shared__ uint8_t exp_of[kRouteChunk * kMaxK];
+  const int t = threadIdx.x;
+  int my[kMaxK], rank[kMaxK];
+  const int tok = (int)walk_choices(idx, perm, t, n, E, k, my);
+  chunk_ranks(my, k, rank, wcnt);
+  tok_of[t] = tok;
 #pragma unroll
   for (int r = 0; r < kMaxK; ++r) {
     if (r < k) {
-      const int e = my[r];
       int s = -1;
-      if (e >= 0) {
-        s = rank[r];
-        for (int w = 0; w < wave; ++w) s += wcnt[w][e];
+      if (my[r] >= 0) {
+        s = (carry ? carry[my[r]] : 0) + rank[r];
+        if (s >= C) s = -1;
       }
-      rank_out[t * k + r] = s;
+      row[t * k + r] = s;
+      exp_of[t * k + r] = (uint8_t)(my[r] >= 0 ? my[r] : 0);
+      if (blockIdx.x == 0 && t < n) slot[tok * k + r] = s;
     }
+  }
+  if (blockIdx.x == 0) {
+    for (int e = t; e < E; e += kRouteChunk) {
+      int tot = carry ? carry[e] : 0;
+#pragma unroll
+      for (int w = 0; w < kRouteWaves; ++w) tot += wcnt[w][e];
+      fill[e] = tot < C ? tot : C;
+    }
+  }
+  __syncthreads();
+  const int nc = d / V;
+  const int64_t gid = (int64_t)blockIdx.x * kRouteChunk + t;
+  const int j = (int)(gid / nc), c = (int)(gid - (int64_t)j * nc);
+  if (j >= n) return;
+  const u32x4 v = *reinterpret_cast<const u32x4*>(x + (int64_t)tok_of[j] * d + (int64_t)c * V);
+  for (int r = 0; r < k; ++r) {
+    const int s = row[j * k + r];
+    if (s >= 0) *reinterpret_cast<u32x4*>(send + eoff<T>(exp_of[j * k + r], s, c * V, d, C)) = v;
   }
 }
 
@@ -270,6 +330,18 @@ size_t dispatch_ws_bytes(const moe_cfg& c) {
 static void dispatch_walk(const moe_cfg& c, const void* x, const int32_t* idx, const int32_t* perm,
                           const int32_t* carry, int32_t* fill, int32_t* slot, void* send_buf, void* ws, hipStream_t s) {
   const int64_t nch = (c.T + kRouteChunk - 1) / kRouteChunk;
+  if (nch == 1) {   // one launch instead of two or three (48 tokens of d 1024: 3.9 + 5.7 -> 5.7 us)
+    auto go = [&](auto tag) {
+      using T = decltype(tag);
+      const int64_t n = c.T * (c.d_model / Vec<T>::N);
+      hipLaunchKernelGGL(dispatch_small_kernel<T>, dim3((unsigned)((n + kRouteChunk - 1) / kRouteChunk)),
+                         dim3(kRouteChunk), 0, s, (const T*)x, idx, perm, carry, fill, slot, (T*)send_buf, (int)c.T,
+                         c.d_model, c.E, c.k, c.C);
+    };
+    if (c.dtype == MOE_BF16) go(uint16_t{});
+    else go(float{});
+    return;
+  }
   int32_t* counts = (int32_t*)ws;
   int32_t* base = counts + nch * c.E;
   int32_t* rank = base + nch * c.E;
@@ -369,19 +441,31 @@ __global__ __launch_bounds__(256) void bpr_key_kernel(const float* __restrict__ 
   if (lane == 0) elem[t] = ((uint64_t)~__float_as_uint((float)imp) << 32) | (uint64_t)t;
 }
 
-constexpr int kSortThreads = 1024;
-constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kDigitBits = 8;
 constexpr int kRadix = 1 << kDigitBits;
 constexpr int kSortPasses = 4;             // the key's low 30 bits: digits of 8, 8, 8, 6 bits
-constexpr int kCntStride = kSortWaves + 1; // counters of one digit (one per wave), padded
-constexpr int kSortTile = 4096;            // elements per sorted tile: 16 waves x 4 rounds of 64
-constexpr int kWaveSpan = kSortTile / kSortWaves;
-constexpr size_t kTileSortLds = 2 * kSortTile * sizeof(uint64_t) + kSortWaves * kRadix * sizeof(uint64_t) +
-                                (kRadix * kCntStride + kSortWaves) * sizeof(int32_t);
-static_assert(kRadix * kSortWaves == 4 * kSortThreads, "scan layout");
+// Elements of a sorted tile, one wave per kWaveSpan of them.  The smallest tile
+// that holds every token needs no merge; with more, 2048 puts the sort on twice
+// the CUs while the merge searches few tiles.  Gate, sort and dispatch on one
+// MI355X (d 256, 32 experts), tiles of 4096 (and always a merge) -> the choice:
+// 700 tokens 40 -> 33 us, 2048 43 -> 37, 4096 48 -> 43, 8192 57 -> 55, 16384 73
+// -> 72; at 32768 tokens 4096 stays (109 against 114).
+template <int TILE>
+struct SortTile {
+  static constexpr int kTile = TILE;
+  static constexpr int kWaveSpan = 256;               // 4 rounds of 64
+  static constexpr int kWaves = TILE / kWaveSpan;
+  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int kCntStride = kWaves + 1;       // counters of one digit (one per wave), padded
+  static constexpr size_t kLds = 2 * TILE * sizeof(uint64_t) + kWaves * kRadix * sizeof(uint64_t) +
+                                 (kRadix * kCntStride + kWaves) * sizeof(int32_t);
+  static_assert(kWaves % 4 == 0 && kRadix * kWaves == 4 * kThreads, "scan layout");
+};
+using SortLarge = SortTile<4096>;
+using SortMid = SortTile<2048>;
+using SortSmall = SortTile<1024>;
 
-// Sorts one tile of up to kSortTile elements in LDS by the key's low 30 bits
+// Sorts one tile in LDS by the key's low 30 bits
 // (importance keys: ~bits of a float in [0, 1], whose two top bits are
 // constant), stably: an LSD radix sort of four passes.  Wave w owns elements
 // [w kWaveSpan, (w + 1) kWaveSpan) of the tile and takes them in rounds of
@@ -418,10 +502,13 @@ __device__ __forceinline__ int few_digits(int dg, bool ok, uint64_t& m0, uint64_
 }
 
 constexpr int kSplStep = 64;                          // a splitter every 64 sorted elements
-constexpr int kSplPerTile = kSortTile / kSplStep;
-__global__ __launch_bounds__(kSortThreads) void bpr_tile_sort_kernel(const uint64_t* __restrict__ in,
+template <class ST>
+__global__ __launch_bounds__(ST::kThreads) void bpr_tile_sort_kernel(const uint64_t* __restrict__ in,
                                                                      uint64_t* __restrict__ out,
-                                                                     uint64_t* __restrict__ spl, int64_t n) {
+                                                                     uint64_t* __restrict__ spl,
+                                                                     int32_t* __restrict__ perm, int64_t n) {
+  constexpr int kSortTile = ST::kTile, kSortWaves = ST::kWaves, kSortThreads = ST::kThreads;
+  constexpr int kWaveSpan = ST::kWaveSpan, kCntStride = ST::kCntStride, kSplPerTile = kSortTile / kSplStep;
   extern __shared__ __attribute__((aligned(16))) unsigned char bpr_lds[];
   uint64_t* buf0 = reinterpret_cast<uint64_t*>(bpr_lds);
   uint64_t* buf1 = buf0 + kSortTile;
@@ -460,8 +547,8 @@ __global__ __launch_bounds__(kSortThreads) void bpr_tile_sort_kernel(const uint6
     }
     __syncthreads();
     // Exclusive scan of the counters in (digit, wave) order; thread tid owns
-    // digit tid / 4, waves 4 (tid % 4) .. + 3.
-    const int d0 = tid >> 2, w0 = (tid & 3) * 4;
+    // digit tid / (waves / 4) and four of its waves.
+    const int d0 = tid / (kSortWaves / 4), w0 = tid % (kSortWaves / 4) * 4;
     int v[4];
     int sum = 0;
 #pragma unroll
@@ -523,6 +610,10 @@ __global__ __launch_bounds__(kSortThreads) void bpr_tile_sort_kernel(const uint6
     }
     __syncthreads();
   }
+  if (perm) {   // the only tile: its order is the whole order
+    for (int i = tid; i < m; i += kSortThreads) perm[i] = (int32_t)(buf0[i] & 0xffffffffu);
+    return;
+  }
   for (int i = tid; i < m; i += kSortThreads) out[t0 + i] = buf0[i];
   for (int i = tid; i * kSplStep < m; i += kSortThreads) spl[(int64_t)blockIdx.x * kSplPerTile + i] = buf0[i * kSplStep];
 }
@@ -534,9 +625,11 @@ __global__ __launch_bounds__(kSortThreads) void bpr_tile_sort_kernel(const uint6
 // splitters of b (every 64th element, in LDS) bound it to a window of at most
 // 63 elements, searched in device memory.
 constexpr int kMergeTiles = 16;   // tiles whose splitters are in LDS at a time
+template <class ST>
 __global__ __launch_bounds__(256) void bpr_merge_kernel(const uint64_t* __restrict__ sorted,
                                                         const uint64_t* __restrict__ spl, int32_t* __restrict__ perm,
                                                         int64_t n) {
+  constexpr int kSortTile = ST::kTile, kSplPerTile = kSortTile / kSplStep;
   __shared__ uint64_t sp[kMergeTiles * kSplPerTile];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool act = i < n;
@@ -606,8 +699,8 @@ __global__ __launch_bounds__(256) void bpr_merge_kernel(const uint64_t* __restri
 }
 
 static size_t bpr_spl_bytes(const moe_cfg& c) {
-  const int64_t ntiles = (c.T + kSortTile - 1) / kSortTile;
-  return ((size_t)ntiles * kSplPerTile * sizeof(uint64_t) + 255) / 256 * 256;
+  const int64_t n = (c.T + SortLarge::kTile - 1) / SortLarge::kTile * SortLarge::kTile;   // enough for either tile
+  return ((size_t)(n / kSplStep) * sizeof(uint64_t) + 255) / 256 * 256;
 }
 size_t dispatch_bpr_ws_bytes(const moe_cfg& c) {
   const size_t a = (dispatch_ws_bytes(c) + 255) / 256 * 256;
@@ -627,14 +720,22 @@ void launch_dispatch_bpr(const moe_cfg& c, const void* x, const float* logits, c
   int32_t* perm = order ? order : (int32_t*)(w + 2 * eb);
   uint64_t* spl = (uint64_t*)(w + 2 * eb + tb);
   if (c.T > 0) {
-    static std::atomic<uint64_t> lds_ok{0};
-    allow_dyn_lds((const void*)bpr_tile_sort_kernel, (int)kTileSortLds, lds_ok);
-    const int64_t ntiles = (c.T + kSortTile - 1) / kSortTile;
     hipLaunchKernelGGL(bpr_key_kernel, dim3((unsigned)((c.T + 3) / 4)), dim3(256), 0, s, logits, idx, e0, c.T, c.E,
                        c.k);
-    hipLaunchKernelGGL(bpr_tile_sort_kernel, dim3((unsigned)ntiles), dim3(kSortThreads), kTileSortLds, s, e0, e1, spl,
-                       c.T);
-    hipLaunchKernelGGL(bpr_merge_kernel, dim3((unsigned)((c.T + 255) / 256)), dim3(256), 0, s, e1, spl, perm, c.T);
+    auto sort = [&](auto tag) {
+      using ST = decltype(tag);
+      static std::atomic<uint64_t> lds_ok{0};
+      allow_dyn_lds((const void*)bpr_tile_sort_kernel<ST>, (int)ST::kLds, lds_ok);
+      const int64_t ntiles = (c.T + ST::kTile - 1) / ST::kTile;
+      hipLaunchKernelGGL(bpr_tile_sort_kernel<ST>, dim3((unsigned)ntiles), dim3(ST::kThreads), ST::kLds, s, e0, e1, spl,
+                         ntiles == 1 ? perm : (int32_t*)nullptr, c.T);
+      if (ntiles > 1)
+        hipLaunchKernelGGL(bpr_merge_kernel<ST>, dim3((unsigned)((c.T + 255) / 256)), dim3(256), 0, s, e1, spl, perm,
+                           c.T);
+    };
+    if (c.T <= SortSmall::kTile) sort(SortSmall{});
+    else if (c.T <= SortMid::kTile || (c.T > SortLarge::kTile && c.T <= 4 * SortLarge::kTile)) sort(SortMid{});
+    else sort(SortLarge{});
   }
   dispatch_walk(c, x, idx, perm, nullptr, fill, slot, send_buf, ws, s);
 }
@@ -1144,12 +1245,12 @@ static void launch_dwg_t(const moe_cfg& c, const void* x, const float* dl, float
 void launch_dwg(const moe_cfg& c, const void* x, const float* dlogits, float* dWg, void* ws, hipStream_t s) {
   const int64_t ed = (int64_t)c.E * c.d_model;   // a multiple of 8
   const DwgPlan q = dwg_plan(c);                 // nch = 0 when T == 0: the reduce then writes zeros
-  float* part = (float*)ws;
+  float* part = q.nch == 1 ? dWg : (float*)ws;   // one chunk's sums are the result: no second launch
   if (q.nch > 0) {
     if (c.dtype == MOE_BF16) launch_dwg_t<uint16_t>(c, x, dlogits, part, q, s);
     else launch_dwg_t<float>(c, x, dlogits, part, q, s);
   }
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((unsigned)((ed / 4 + 31) / 32)), dim3(32 * kDwgRuns), 0, s, part,
+  if (q.nch != 1) hipLaunchKernelGGL(dwg_reduce_kernel, dim3((unsigned)((ed / 4 + 31) / 32)), dim3(32 * kDwgRuns), 0, s, part,
                      dWg, (int)q.nch, ed);
 }
 
