@@ -327,7 +327,8 @@ __device__ __forceinline__ WSched wide_sched(int n, int nslot, bool allow_split)
 }
 
 // Lane-per-group tile counts of a wide product and their prefixes (groups <= 64).
-// Ragged-K, or ragged-M without SEP: every tile of a group (with rows).
+// Ragged-K, or ragged-M without SEP: every tile of a group (with rows); ragged-K
+// prefixes run over the groups by rows, most first.
 // Ragged-M with SEP: the full M-tiles (256 rows) and, separately, the short
 // last M-tile of a group whose rows are not a multiple of 256; tile numbers
 // [0, NF) are the full tiles, [NF, NF + NP) the short ones, so a schedule can
@@ -358,10 +359,26 @@ __device__ __forceinline__ WPrefix wide_tile_prefix(const GemmParams& p, int lan
     }
   }
   WPrefix P;
-  P.incl = cnt;
-  P.inclP = cntP;
   P.lo = lo;
   P.span = span;
+  if constexpr (RAGGED_K) {
+    // Groups by rows, most first (ties by index): a tile is as long as its group,
+    // and a round of the schedule then holds tiles of nearly one length.
+    int before = 0, all = 0;
+    for (int h = 0; h < groups; ++h) {
+      const int ch = __builtin_amdgcn_readlane(cnt, h), sh = __builtin_amdgcn_readlane(span, h);
+      all += ch;
+      if (sh > span || (sh == span && h < lane)) before += ch;
+    }
+    P.excl = before;
+    P.incl = before + cnt;
+    P.inclP = P.exclP = 0;
+    P.NF = all;
+    P.NP = 0;
+    return P;
+  }
+  P.incl = cnt;
+  P.inclP = cntP;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const int u = __shfl_up(P.incl, o, 64);
@@ -391,7 +408,9 @@ __device__ __forceinline__ WGeo wide_geo(const GemmParams& p, int t, int lane, i
   const int tt = shrt ? t - P.NF : t;
   const int inc = shrt ? P.inclP : P.incl;
   const int exc = shrt ? P.exclP : P.excl;
-  G.g = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < groups && inc <= tt)));
+  // The group holding tile tt: by its own range (ragged-K: groups in row order), or counting the groups before it.
+  G.g = RAGGED_K ? __builtin_ctzll(__ballot(lane < groups && exc <= tt && tt < inc) | (1ull << 63))
+                 : __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < groups && inc <= tt)));
   const int local = tt - __builtin_amdgcn_readlane(exc, G.g);
   const int lo = __builtin_amdgcn_readlane(P.lo, G.g);
   int span = __builtin_amdgcn_readlane(P.span, G.g);
@@ -604,7 +623,9 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // ragged-K products, whose tiles cost as many K-steps as their group has
   // rows, take every eighth tile, so each XCD gets an even share of every
   // group (with skewed routing, a contiguous range could hold the few large
-  // groups).  xtile(j) = the XCD's j-th tile.
+  // groups), longest groups first.  xtile(j) = the XCD's j-th tile.  (In index
+  // order the large groups' tiles met on the same slots: dW of 32768 tokens over
+  // 64 experts, Zipf 1.2, 220 to 265 us by where they stood; by rows 190 to 201.)
   // The block's segments (see WSched): nd whole tiles xtile(e nslot + slot),
   // then, if the last round is K-split (ragged-M products, one K length), the
   // K range [sk0, sk1) of remainder tile xtile(R nslot + sq).
@@ -620,7 +641,11 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   sq = __builtin_amdgcn_readfirstlane(sq);
   sk0 = __builtin_amdgcn_readfirstlane(sk0);
   sk1 = __builtin_amdgcn_readfirstlane(sk1);
-  const int nd = __builtin_amdgcn_readfirstlane(W.R + (!W.split && slot < W.r ? 1 : 0));
+  // Ragged-K rounds run through the slots forth and back (as the groups come
+  // longest first, a slot that got the longer tile of one round gets the shorter
+  // of the next).
+  auto slot_of = [&](int e) __attribute__((always_inline)) { return RAGGED_K && (e & 1) ? nslot - 1 - slot : slot; };
+  const int nd = __builtin_amdgcn_readfirstlane(W.R + (!W.split && slot_of(W.R) < W.r ? 1 : 0));
   const int nseg = __builtin_amdgcn_readfirstlane(nd + (SPLIT && W.split && sk0 < sk1 ? 1 : 0));
   if (nseg == 0) return;
 
@@ -631,7 +656,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // Segment e: tile, first K-step, end K-step (0 = the tile's own count).
   auto seg = [&](int e, int& t, int& k0, int& k1) __attribute__((always_inline)) {
     if (e < nd) {
-      t = xtile(e * nslot + slot);
+      t = xtile(e * nslot + slot_of(e));
       k0 = 0;
       k1 = 0;
     } else {
