@@ -66,7 +66,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 #: HBM bytes per call from PMC counters (profiles/*_pmc_traffic.md), each valid for the
 #: workload, call and GEMM sources it names.
 PROFILES = os.path.join(ROOT, "profiles")
-GEMM_SOURCES = ["paper_2404_19429_amd/csrc/gemm.hip", "paper_2404_19429_amd/csrc/lds_ops.h",
+GEMM_SOURCES = ["paper_2404_19429_amd/csrc/gemm.hip", "paper_2404_19429_amd/csrc/gemm_wide.h",
+                "paper_2404_19429_amd/csrc/gemm_256x256.hip", "paper_2404_19429_amd/csrc/lds_ops.h",
                 "paper_2404_19429_amd/csrc/common.h"]
 
 
