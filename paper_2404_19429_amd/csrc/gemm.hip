@@ -288,8 +288,8 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
 
 // Expert products.  bf16: blocked operands, wide tiles; outputs that a later
 // product reads (H, A, dH) blocked, the others (expert_out, dXe, which only
-// the gathers read, and the dW products) row-major.  float: the FMA kernel,
-// row-major.
+// the gathers read, and the dW products) row-major.  float: the float MFMA
+// kernel, row-major.
 // rows: rows of the output per group (ragged-M: the capacity C, with up to 15
 // alignment rows; ragged-K: M); cols: N.
 template <bool B_K, bool RAGGED_K, int EPI>

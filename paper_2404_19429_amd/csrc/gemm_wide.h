@@ -84,10 +84,9 @@ constexpr int kPanelN = 8;
 // The expert products at full size.  256 x 256 block tiles, one block per CU,
 // eight waves in a 2 x 4 grid, each owning a 128 x 64 tile (32 accumulator
 // fragments) -- two waves per SIMD, so one wave's MFMAs issue while the other
-// waits on memory (a four-wave 128 x 128 variant is kept for comparison).
-// Against 128 x 128 block tiles this halves the operand bytes a CU moves
-// global -> LDS per flop; the per-CU load path is what limits the smaller
-// tile.
+// waits on memory.  Against 128 x 128 block tiles this halves the operand
+// bytes a CU moves global -> LDS per flop; the per-CU load path is what limits
+// the smaller tile.
 //
 // Operands reach LDS through raw buffer loads with the LDS flag: a scalar
 // buffer descriptor covers the operand's group from the current K-step on, so
@@ -113,7 +112,8 @@ constexpr int kPanelN = 8;
 // The product is computed transposed (MFMA A operand = a B fragment, B operand
 // = an A fragment), so each lane's four accumulator values are four
 // consecutive output columns of one row: the epilogue converts them with
-// v_cvt_pk_bf16_f32 and stores 8-byte vectors straight from registers.
+// v_cvt_pk_bf16_f32, swaps halves of two fragments between lane groups and
+// stores 16-byte vectors straight from registers.
 //
 // LDS stages: four with one block barrier per K-step; five (the whole LDS)
 // with one barrier per two K-steps (PAIR: the barrier before an even step
