@@ -277,8 +277,16 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
     // tokens, d 768, 8 experts, 288 large tiles: 43 -> 32 us; of 20000 tokens,
     // d 512, 128 large tiles: 82 -> 57); with more the larger tile wins (8192
     // tokens, d 1024, 16 experts, 1024 large tiles: 142 against 166).
+    // Groups known to be equally long and not short (w.expect, the dense weight
+    // gradients' token ranges): whole rounds decide, 256-tiles one per CU, 128-tiles
+    // three per CU (192 large tiles' work) in 3/4 of the time.  dW of 256 large tiles
+    // and 8192 rows each, 128- against 256-tiles (two launches) 645 and 505 us, of 416
+    // tiles and 1260 rows 191 and 170; of 512 tiles and 75 rows 45 and 50.  Routed
+    // groups may be skewed, which the smaller tile spreads better.
     const int64_t large = (w.rows + 255) / 256 * ((w.cols + 255) / 256) * w.groups;
-    return large <= 512 ? run_wide_128x128(w, s) : run_wide_256x256(w, s);
+    const bool small = w.kind == WK_WGF32 && w.expect >= 512. ? 3 * ((large + 191) / 192) < 4 * ((large + 255) / 256)
+                                                              : true;
+    return small && large <= 512 ? run_wide_128x128(w, s) : run_wide_256x256(w, s);
   }
   const TileCost* best = &kTilesM[0];
   for (const TileCost& t : kTilesM)
@@ -496,7 +504,7 @@ void launch_dense_wgrad(int M, int N, int64_t K, const void* A, const void* B, v
   const int64_t MN = (int64_t)M * N;
   GemmParams p{A, M, 0, B, N, 0, part, N, MN, nullptr, nullptr, nullptr, nullptr, M, N, 0, 0, (int)K};
   p.kchunk = (int)(((K + S - 1) / S + 31) / 32 * 32);
-  run_wide_any(WideCall{WK_WGF32, MOE_ACT_IDENTITY, S, M, N, 0., 0., p}, s);
+  run_wide_any(WideCall{WK_WGF32, MOE_ACT_IDENTITY, S, M, N, (double)std::min<int64_t>(K, p.kchunk), 0., p}, s);
   hipLaunchKernelGGL(gemm_wgrad_reduce_kernel, dim3((unsigned)((MN / 8 + 255) / 256)), dim3(256), 0, s,
                      (const float*)part, S, MN, (uint16_t*)C);
 }

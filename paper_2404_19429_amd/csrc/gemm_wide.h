@@ -1085,7 +1085,7 @@ struct WideCall {
   int groups;
   int64_t rows;   // rows of the output per group (ragged-M: the capacity; ragged-K: M)
   int cols;       // N
-  double expect;  // ragged-M: rows a group is expected to hold, and their
+  double expect;  // rows a group is expected to hold (WK_WGF32: its K), and their
   double spread;  // standard deviation (hints for the tile choice)
   GemmParams p;
 };
