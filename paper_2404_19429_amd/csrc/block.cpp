@@ -119,8 +119,8 @@ WsLayout ws_layout(const moe_block_cfg& c, int n) {
   size_t off = 0;
   L.disp = off; off += align256(dispatch_ws_bytes(part));
   L.dw = off;   off += align256(bwd_dw_ws_bytes(c.moe));
-  L.ln2 = off;  off += align256((size_t)ln_bwd_blocks(T) * 2 * d * sizeof(float));
-  L.ln1 = off;  off += align256((size_t)ln_bwd_blocks(T) * 2 * d * sizeof(float));
+  L.ln2 = off;  off += align256((size_t)ln_bwd_most_blocks(T) * 2 * d * sizeof(float));
+  L.ln1 = off;  off += align256((size_t)ln_bwd_most_blocks(T) * 2 * d * sizeof(float));
   L.sk = off;   off += align256(expert_sk_ws_bytes(c.moe));   // expert products on the compute stream
   // Blocked copies for the dense products on the wide kernel: Wqkv, Wo, and
   // one activation operand at a time (used in turn on the compute stream).

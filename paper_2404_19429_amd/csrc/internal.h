@@ -134,8 +134,11 @@ void launch_attn_bwd(const void* qkv, const void* o, const void* dout, const flo
 // norm.hip: LayerNorm (eps 1e-5) of bf16 rows of width d (multiple of 8, <= 4096).
 // The backward writes ln_bwd_blocks(T) x 2 x d float partials, reduced by
 // launch_ln_gain_reduce into the gain and bias gradients (the reduction
-// overwrites some partials: run it once per backward).
+// overwrites some partials: run it once per backward).  A workspace holds
+// ln_bwd_most_blocks(T) x 2 x d, the largest over every row count up to T, so
+// that one sized for the longest batch serves the shorter ones.
 int ln_bwd_blocks(int64_t T);
+int ln_bwd_most_blocks(int64_t T);
 // y_blk / dx_blk non-null (d a multiple of 32): the output is also written in
 // the 16 x 32 blocked layout of the dense products (padding rows not written).
 void launch_ln_fwd(const void* x, const void* g, const void* b, void* y, float* mean, float* rstd, int64_t T, int d,

@@ -24,7 +24,8 @@ constexpr int kLnMaxChunks = 8;   // chunks per lane: d <= 64 * 8 * 8 = 4096
 // another, each a load latency, so up to 8192 rows two per wave (twice to four
 // times the blocks); with more rows the chip is full and eight keep the partial
 // sums few.  One MI355X, 3108 rows of 768: 20.8 -> 10.0 us.
-static int ln_bwd_rpw(int64_t T) { return T <= 8192 ? 2 : 8; }
+constexpr int64_t kLnShortRows = 8192;
+static int ln_bwd_rpw(int64_t T) { return T <= kLnShortRows ? 2 : 8; }
 
 // Nearest-even bf16 of a double, rounded once: round the significand to 8
 // bits in double, after which the value converts to float exactly.
@@ -229,6 +230,8 @@ static int ln_chunks(int d) {
 }
 
 int ln_bwd_blocks(int64_t T) { return (int)((T + 4 * ln_bwd_rpw(T) - 1) / (4 * ln_bwd_rpw(T))); }
+// (ln_bwd_blocks falls from 1024 to 257 past kLnShortRows)
+int ln_bwd_most_blocks(int64_t T) { return std::max(ln_bwd_blocks(T), ln_bwd_blocks(std::min(T, kLnShortRows))); }
 
 void launch_ln_fwd(const void* x, const void* g, const void* b, void* y, float* mean, float* rstd, int64_t T, int d,
                    hipStream_t s, void* y_blk) {

@@ -149,6 +149,15 @@ def test_block_workspace_bytes():
     assert L.moe_block_workspace_bytes(_bcfg(), 3) == 0 and "n_chunks" in L.moe_last_error()
 
 
+@pytest.mark.parametrize("heads", [1, 8, 32])
+def test_block_workspace_of_a_longer_batch_serves_a_shorter_one(heads):
+    """A program allocates once, for its longest batch: the size never falls with
+    the rows (among them 8192, where the LayerNorm backward's split changes)."""
+    need = [L.moe_block_workspace_bytes(_bcfg(B=1, S=S, heads=heads, d_ff=512, E=8, C=S), 1)
+            for S in (1, 2000, 8185, 8192, 8193, 9000, 10000, 16384, 32768)]
+    assert need[0] > 0 and need == sorted(need), need
+
+
 def test_block_valid_call_without_gpu_reports_device_error():
     assert _block_call(_bcfg(), 4) == L.MOE_EDEVICE
 
