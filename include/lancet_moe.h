@@ -197,7 +197,9 @@ moe_status moe_dispatch_bpr(const moe_cfg* cfg, const void* x, const float* logi
 /* Expert weights in the layout the expert GEMMs read, written once per
  * weight update and used by moe_expert_ffn_fwd and moe_bwd_dx:
  *   W1 [E][f][d], W2 [E][d][f] row-major dtype -> W1p [E][f][d], W2p [E][d][f]
- *   in the expert-buffer layout above (bf16: blocks; float: a plain copy). */
+ *   in the expert-buffer layout above (bf16: blocks; float: a plain copy).
+ *   W1p may share no memory with W1, W2 or W2p, and W2p none with W2; W2p may
+ *   be the memory of W1, which is packed before it is overwritten. */
 moe_status moe_pack_weights(const moe_cfg* cfg, const void* W1, const void* W2, void* W1p, void* W2p,
                             moe_stream_t stream);
 

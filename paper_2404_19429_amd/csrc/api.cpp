@@ -280,7 +280,7 @@ moe_status moe_pack_weights(const moe_cfg* cfg, const void* W1, const void* W2, 
   const char* fn = "moe_pack_weights";
   CHECK(check_cfg(cfg, fn, true));
   REQUIRE_PTR(W1); REQUIRE_PTR(W2); REQUIRE_PTR(W1p); REQUIRE_PTR(W2p);
-  if (W1 == W1p || W2 == W2p || W1p == W2p) return fail(MOE_EINVAL, "%s: packed and source weights may not alias", fn);
+  if (W1 == W1p || W2 == W2p || W1p == W2p || W1p == W2) return fail(MOE_EINVAL, "%s: packed and source weights may not alias", fn);
   CHECK(check_device(fn));
   lmoe::launch_pack_weights(*cfg, W1, W2, W1p, W2p, (hipStream_t)stream);
   return check_launch(fn);

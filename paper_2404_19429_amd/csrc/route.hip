@@ -1302,13 +1302,17 @@ __global__ __launch_bounds__(256) void copy_weights_kernel(const u32x4* __restri
 
 void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void* W1p, void* W2p, hipStream_t s) {
   const int64_t E = c.E, d = c.d_model, f = c.d_ff;
+  // Both matrices in one launch, unless W2p lies over W1: then W1 is read whole
+  // before W2p is written.
+  const size_t bytes = (size_t)(E * f * d) * (c.dtype == MOE_BF16 ? 2 : 4);
+  const bool over = (uintptr_t)W2p < (uintptr_t)W1 + bytes && (uintptr_t)W1 < (uintptr_t)W2p + bytes;
   if (c.dtype == MOE_BF16) {
     const int64_t n1 = E * (f / 16) * ((d + 127) / 128), n2 = E * (d / 16) * ((f + 127) / 128);
     auto go = [&](int64_t b1, int64_t b2) {
       hipLaunchKernelGGL(pack_blocked_kernel, dim3((unsigned)(b1 + b2)), dim3(256), 0, s, (const uint16_t*)W1,
                          (uint16_t*)W1p, (int)d, b1, (const uint16_t*)W2, (uint16_t*)W2p, (int)f);
     };
-    if (n1 + n2 <= 1 << 23) {
+    if (n1 + n2 <= 1 << 23 && !over) {
       go(n1, n2);
     } else {   // (the launch's thread count is 32 bits)
       go(n1, 0);
@@ -1323,7 +1327,8 @@ void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void*
                            (const u32x4*)W1 + o, (u32x4*)W1p + o, one ? b : 0, (const u32x4*)W2 + o, (u32x4*)W2p + o, m);
       }
     };
-    go(true, true);
+    go(true, !over);
+    if (over) go(false, true);
   }
 }
 

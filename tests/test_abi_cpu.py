@@ -194,6 +194,10 @@ def test_pack_weights_validation():
     assert lib.moe_pack_weights(ctypes.byref(c), GOOD, GOOD * 2, GOOD * 3, GOOD * 4, None) == L.MOE_EDEVICE
     assert lib.moe_pack_weights(ctypes.byref(c), GOOD, GOOD * 2, GOOD, GOOD * 4, None) == L.MOE_EINVAL
     assert lib.moe_pack_weights(ctypes.byref(c), GOOD, GOOD * 2, None, GOOD * 4, None) == L.MOE_EINVAL
+    # W1's copy over W2: the source would be gone before it is read; W2's copy over W1 is in order
+    assert lib.moe_pack_weights(ctypes.byref(c), GOOD, GOOD * 2, GOOD * 2, GOOD * 4, None) == L.MOE_EINVAL
+    assert "alias" in L.moe_last_error()
+    assert lib.moe_pack_weights(ctypes.byref(c), GOOD, GOOD * 2, GOOD * 3, GOOD, None) == L.MOE_EDEVICE
     assert lib.moe_pack_weights(ctypes.byref(_cfg(d_model=72)), GOOD, GOOD * 2, GOOD * 3, GOOD * 4, None) == L.MOE_ESHAPE
 
 

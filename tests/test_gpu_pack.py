@@ -46,3 +46,14 @@ def test_pack_weights_layout(L, dtype, E, d, f):
     assert torch.equal(buf[0, :n].view(E, f, d), _packed(W1, dtype))
     assert torch.equal(buf[1, :n].view(E, d, f), _packed(W2, dtype))
     assert bool(buf[:, n:].isnan().all())
+
+
+@pytest.mark.parametrize("dtype,E,d,f", SHAPES)
+def test_copy_of_w2_may_take_the_memory_of_w1(L, dtype, E, d, f):
+    cfg, W1, W2 = _weights(L, dtype, E, d, f)
+    want1, want2 = _packed(W1, dtype).clone(), _packed(W2, dtype).clone()
+    W1p = torch.empty_like(W1)
+    L.moe_pack_weights(cfg, W1, W2, W1p, W1)
+    torch.cuda.synchronize()
+    assert torch.equal(W1p, want1)
+    assert torch.equal(W1.view(E, d, f), want2)
