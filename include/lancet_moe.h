@@ -409,8 +409,8 @@ size_t moe_block_workspace_bytes(const moe_block_cfg* cfg, int32_t n_chunks);
  *   is done -- starting from the capacity partition i-1 left, so routing,
  *   slots and drops equal the unpartitioned layer -- and its combine (plus the
  *   residual h) as soon as its experts are done (the last combine, and with
- *   n_chunks = 1 the dispatch, overlap nothing: streams[0] runs them).
- *   Partition i's dispatch thus
+ *   n_chunks = 1 the dispatch, overlap nothing: streams[0] runs them, after the
+ *   earlier and before the later work on streams[1]).  Partition i's dispatch thus
  *   overlaps partition i+1's attention, and its combine the next partition's
  *   experts.  The block's expert products never split a K sum (moe.ksplit
  *   is ignored and taken as 0), so every output is bitwise independent of
@@ -422,7 +422,8 @@ size_t moe_block_workspace_bytes(const moe_block_cfg* cfg, int32_t n_chunks);
  *   x [T][d], out [T][d], dy [T][d], dx [T][d], bf16.  The backward reads the
  *   forward's acts (a forward with the same n_chunks must precede it).
  *   streams: three hipStream_t (entries may repeat).  When the call returns,
- *   all its work is ordered before any later work on streams[0].
+ *   all its work is ordered before any later work on streams[0], and the
+ *   forward's before any later work on streams[1].
  *   ws: moe_block_workspace_bytes(cfg, n_chunks) bytes.
  *   Errors: n_chunks must divide B (1 <= n_chunks <= 64); d_model = 128 heads
  *   <= 4096; d_ff a multiple of 64; moe.T = B*S. */

@@ -69,6 +69,16 @@ hipError_t order(hipStream_t a, hipStream_t b) {
   return hipStreamWaitEvent(b, ev, 0);
 }
 
+// b waits for the caller's earlier work on a.  In a capture of b, a stream that
+// is not part of it has none that the graph could wait for.
+hipError_t order_earlier(hipStream_t a, hipStream_t b) {
+  hipStreamCaptureStatus ca = hipStreamCaptureStatusNone, cb = hipStreamCaptureStatusNone;
+  if (a == b) return hipSuccess;
+  HIP_TRY(hipStreamIsCapturing(b, &cb));
+  if (cb != hipStreamCaptureStatusNone) HIP_TRY(hipStreamIsCapturing(a, &ca));
+  return ca == cb ? order(a, b) : hipSuccess;
+}
+
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 // Timing events of this thread's last timed backward: start and end of each
@@ -185,8 +195,10 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
     moe_cfg pc = mc;
     pc.T = Tc;
     // One partition's data movement has nothing to overlap: it stays on the
-    // compute stream, and so does the last partition's combine (each crossing of
-    // streams costs about 10 us; block forward of 500 tokens 199 -> 146 us).
+    // compute stream, and so does the last partition's combine (a crossing of
+    // streams on the way costs about 13 us; block forward of 500 tokens 199 -> 146
+    // us).  It still comes after the caller's earlier work on the data-movement
+    // stream and before its later work there (3 and 16 us of that forward).
     const hipStream_t Sd = n == 1 ? Sc : Sx;
     HIP_TRY(order(Sc, Sd));  // the data-movement stream starts after the caller's earlier work
     if (!mc.wpacked) launch_pack_weights(mc, W.W1, W.W2, A.W1p, A.W2p, Sc);  // expert weights as the GEMMs read them
@@ -206,7 +218,7 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       launch_ln_fwd(bf(A.h, t0 * d), W.ln2_g, W.ln2_b, bfm(A.m, t0 * d), A.ln2_mean + t0, A.ln2_rstd + t0, Tc, d, Sc);
       launch_gate(pc, bf(A.m, t0 * d), W.Wg, nullptr, A.logits + t0 * E, A.idx + t0 * k, A.w + t0 * k, Sc);
       HIP_TRY(hipGetLastError());
-      HIP_TRY(order(Sc, Sd));
+      HIP_TRY(n == 1 ? order_earlier(Sx, Sc) : order(Sc, Sx));
       launch_dispatch(pc, bf(A.m, t0 * d), A.idx + t0 * k, i == 0 ? nullptr : A.fill + (int64_t)(i - 1) * E,
                       A.fill + (int64_t)i * E, A.slot + t0 * k, A.send_buf, wsb + L.disp, Sd);
       HIP_TRY(hipGetLastError());
@@ -215,7 +227,7 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
         HIP_TRY(hipEventRecord(ev_disp[i], Sd));
       }
     }
-    for (int i = 0; i < n; ++i) {  // expert stage, partitions in order; each combine follows on Sx
+    for (int i = 0; i < n; ++i) {  // expert stage, partitions in order; each combine follows on Sx, the last on Sc
       const int64_t t0 = Tc * i;
       if (Sd != Sc) HIP_TRY(hipStreamWaitEvent(Sc, ev_disp[i], 0));
       const int32_t* rb = i == 0 ? nullptr : A.fill + (int64_t)(i - 1) * E;
@@ -228,6 +240,7 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       HIP_TRY(hipGetLastError());
     }
     HIP_TRY(order(Sd, Sc));
+    HIP_TRY(order(Sc, Sx));
   }
 
   if (passes & MOE_BLOCK_BWD) {

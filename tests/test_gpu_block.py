@@ -195,6 +195,38 @@ def test_forward_then_backward_passes_equal_combined(L):
     _assert_bitwise(b1, b2, spec.moe.E, "separate passes")
 
 
+@pytest.mark.parametrize("n", [1, 2])
+def test_forward_is_ordered_with_the_data_movement_stream(L, n):
+    """streams[1] alone orders a caller's work with the forward, whichever stream
+    runs the dispatch and the last combine: an earlier read of send_buf there sees
+    the old contents, a later read of out the new ones (each stream is held back
+    by some milliseconds of other work, so that an unordered read would be early)."""
+    spec = SMALL["B4_S37_d128_f128_E4_4chunks"]
+    dev = _upload(L, block_inputs(spec))
+    _, _, ref = run_block(L, spec, dev, n, passes=L.MOE_BLOCK_FWD)
+    cfg, C = _cfg(L, spec)
+    w, x, dy = dev
+    b = L.alloc_block(cfg, n)
+    b["send_buf"].fill_(3)
+    out = torch.zeros_like(x)
+    ballast = torch.zeros(1 << 27, device="cuda")
+    s = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s[1]):
+        for _ in range(40):
+            ballast.add_(1)
+        before = b["send_buf"].clone()
+    with torch.cuda.stream(s[0]):
+        for _ in range(40):
+            ballast.add_(1)
+    L.moe_block_chunked(cfg, w, None, x, out, None, None, b, L.MOE_BLOCK_FWD, n, s, b["ws"])
+    with torch.cuda.stream(s[1]):
+        after = out.clone()
+    torch.cuda.synchronize()
+    assert bool((before == 3).all())
+    assert torch.equal(after, ref["out"])
+
+
 # ------------------------------------------------------------------ full size
 @pytest.fixture(scope="module")
 def full(L):

@@ -124,3 +124,43 @@ def test_graph_replay_full_size_equals_eager(L):
         torch.cuda.synchronize()
         for n in names:
             assert torch.equal(getattr(b, n), getattr(ref_b, n)), f"{n} differs on replay {rep}"
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_block_captured_on_three_streams_replays_equal_eager(L, n):
+    """A block step whose two side streams are not part of the capture before the
+    call: it brings them in, joins them, and every replay gives the eager bits."""
+    from synth import block_inputs, block_spec
+    from oracle import moe_oracle as O
+    spec = block_spec(B=2, S=100, d=256, heads=2, moe_f=256, moe_E=8, n_chunks=n, seed=24)
+    m = spec.moe
+    C = O.capacity(spec.B * spec.S, m.E, m.k, m.cf_num, m.cf_den)
+    cfg = L.make_block_cfg(spec.B, spec.S, spec.heads, m.f, m.E, m.k, C, m.G, m.act, m.renorm)
+    inp = block_inputs(spec)
+    w = {q: to_dev(inp[q], torch.bfloat16).reshape(-1) for q in L.BLOCK_WEIGHTS}
+    x, dy = (to_dev(inp[q], torch.bfloat16).reshape(-1) for q in ("x", "dy"))
+    side = [torch.cuda.Stream() for _ in range(2)]
+
+    def buffers():
+        b = L.alloc_block(cfg, n)
+        b["out"], b["dx"] = torch.empty_like(x), torch.empty_like(x)
+        return b
+
+    def step(b):
+        L.moe_block_chunked(cfg, w, b, x, b["out"], dy, b["dx"], b, 3, n, [torch.cuda.current_stream()] + side, b["ws"])
+
+    ref, b = buffers(), buffers()
+    step(ref)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(b)
+    names = ["out", "dx"] + L.BLOCK_GRADS
+    for rep in range(3):
+        for q in names:
+            b[q].fill_(float("nan"))
+        graph.replay()
+        step(ref)                                # eager work between replays
+        torch.cuda.synchronize()
+        for q in names:
+            assert torch.equal(b[q], ref[q]), f"{q} differs on replay {rep}"
