@@ -36,6 +36,16 @@ constexpr auto kBf16 = at::kBFloat16;
 constexpr auto kF32 = at::kFloat;
 constexpr auto kI32 = at::kInt;
 
+// Element counts before the C ABI has checked the sizes they come from: a product
+// of four 31-bit factors, or of 63 and 31 bits, is exact.
+using Num = __int128;
+std::string str(Num v) {
+  std::string s;
+  const bool neg = v < 0;
+  for (unsigned __int128 u = neg ? -(unsigned __int128)v : v; u || s.empty(); u /= 10) s.insert(s.begin(), '0' + (int)(u % 10));
+  return neg ? "-" + s : s;
+}
+
 const char* type_name(at::ScalarType t) {
   switch (t) {
     case at::kBFloat16: return "torch.bfloat16";
@@ -47,7 +57,7 @@ const char* type_name(at::ScalarType t) {
 }
 
 // The pointer of tensor o (NULL for an absent or empty one), checked.
-void* ptr(PyObject* o, const char* name, at::ScalarType type, int64_t numel, bool nullable = false) {
+void* ptr(PyObject* o, const char* name, at::ScalarType type, Num numel, bool nullable = false) {
   if (o == Py_None) {
     if (nullable) return nullptr;
     PyErr_Format(PyExc_ValueError, "%s is required", name);
@@ -73,8 +83,8 @@ void* ptr(PyObject* o, const char* name, at::ScalarType type, int64_t numel, boo
     throw Error();
   }
   if (t.numel() < numel) {
-    PyErr_Format(PyExc_ValueError, "%s has %lld elements, the call touches %lld", name, (long long)t.numel(),
-                 (long long)numel);
+    PyErr_Format(PyExc_ValueError, "%s has %lld elements, the call touches %s", name, (long long)t.numel(),
+                 str(numel).c_str());
     throw Error();
   }
   return t.numel() ? t.data_ptr() : nullptr;
@@ -104,9 +114,19 @@ struct Struct {
 
 at::ScalarType dtype_of(const moe_cfg* c) { return c->dtype == MOE_BF16 ? kBf16 : kF32; }
 // Elements of an [E][C][X] expert buffer.
-int64_t expert_numel(const moe_cfg* c, int64_t X) {
-  const int64_t rows = c->dtype == MOE_BF16 ? ((int64_t)c->C + 15) / 16 * 16 : c->C;
+Num expert_numel(const moe_cfg* c, Num X) {
+  const Num rows = c->dtype == MOE_BF16 ? ((Num)c->C + 15) / 16 * 16 : c->C;
   return c->E * rows * X;
+}
+
+// An integer argument, its magnitude bounded to 64 bits.
+Num big(PyObject* o) {
+  PyObject* i = PyNumber_Index(o);
+  if (!i) throw Error();
+  int over = 0;
+  const long long v = PyLong_AsLongLongAndOverflow(i, &over);
+  Py_DECREF(i);
+  return over ? (Num)over << 64 : (Num)v;
 }
 
 void* stream_arg(PyObject* o) {
@@ -149,7 +169,7 @@ ENTRY(gate_topk) {   // cfg, x, Wg, bias, logits, idx, w, stream
   return entry(n, 8, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t T = c->T, d = c->d_model, E = c->E, k = c->k;
+    const Num T = c->T, d = c->d_model, E = c->E, k = c->k;
     const void* x = ptr(a[1], "x", dt, T * d);
     const void* Wg = ptr(a[2], "Wg", dt, E * d);
     const float* bias = (const float*)ptr(a[3], "bias", kF32, E, true);
@@ -165,7 +185,7 @@ ENTRY(gate_topk) {   // cfg, x, Wg, bias, logits, idx, w, stream
 PyObject* dispatch_any(PyObject* const* a, bool ws_arg) {
   Struct<moe_cfg> c(a[0]);
   const auto dt = dtype_of(c);
-  const int64_t T = c->T, d = c->d_model, E = c->E, k = c->k;
+  const Num T = c->T, d = c->d_model, E = c->E, k = c->k;
   const size_t need = ws_arg ? g_abi.workspace_bytes(c, MOE_CALL_DISPATCH) : 0;
   const void* x = ptr(a[1], "x", dt, T * d);
   const int32_t* idx = (const int32_t*)ptr(a[2], "idx", kI32, T * k);
@@ -189,7 +209,7 @@ ENTRY(dispatch_bpr) {   // cfg, x, logits, idx, fill, slot, send_buf, order, ws,
   return entry(n, 10, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t T = c->T, d = c->d_model, E = c->E, k = c->k;
+    const Num T = c->T, d = c->d_model, E = c->E, k = c->k;
     const size_t need = g_abi.workspace_bytes(c, MOE_CALL_DISPATCH_BPR);
     const void* x = ptr(a[1], "x", dt, T * d);
     const float* logits = (const float*)ptr(a[2], "logits", kF32, T * E);
@@ -209,7 +229,7 @@ ENTRY(pack_weights) {   // cfg, W1, W2, W1p, W2p, stream
   return entry(n, 6, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t m = (int64_t)c->E * c->d_ff * c->d_model;
+    const Num m = (Num)c->E * c->d_ff * c->d_model;
     const void* W1 = ptr(a[1], "W1", dt, m);
     const void* W2 = ptr(a[2], "W2", dt, m);
     void* W1p = ptr(a[3], "W1p", dt, m);
@@ -223,7 +243,7 @@ ENTRY(expert_ffn_fwd) {   // cfg, send_buf, row_begin, row_end, W1p, W2p, H, A, 
   return entry(n, 11, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t d = c->d_model, f = c->d_ff, E = c->E;
+    const Num d = c->d_model, f = c->d_ff, E = c->E;
     const size_t need = g_abi.workspace_bytes(c, MOE_CALL_FFN_FWD);
     const void* send = ptr(a[1], "send_buf", dt, expert_numel(c, d));
     const int32_t* rb = (const int32_t*)ptr(a[2], "row_begin", kI32, E, true);
@@ -244,7 +264,7 @@ ENTRY(combine) {   // cfg, expert_out, idx, slot, w, y, stream
   return entry(n, 7, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t T = c->T, d = c->d_model, k = c->k;
+    const Num T = c->T, d = c->d_model, k = c->k;
     const void* O = ptr(a[1], "expert_out", dt, expert_numel(c, d));
     const int32_t* idx = (const int32_t*)ptr(a[2], "idx", kI32, T * k);
     const int32_t* slot = (const int32_t*)ptr(a[3], "slot", kI32, T * k);
@@ -260,8 +280,8 @@ ENTRY(bwd_dx) {
   return entry(n, 20, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t T = c->T, d = c->d_model, f = c->d_ff, E = c->E, k = c->k;
-    const int64_t nd = expert_numel(c, d), nf = expert_numel(c, f);
+    const Num T = c->T, d = c->d_model, f = c->d_ff, E = c->E, k = c->k;
+    const Num nd = expert_numel(c, d), nf = expert_numel(c, f);
     const size_t need = g_abi.workspace_bytes(c, MOE_CALL_BWD_DX);
     const void* Wg = ptr(a[1], "Wg", dt, E * d);
     const float* logits = (const float*)ptr(a[2], "logits", kF32, T * E);
@@ -294,8 +314,8 @@ ENTRY(bwd_dw) {
   return entry(n, 14, [&] {
     Struct<moe_cfg> c(a[0]);
     const auto dt = dtype_of(c);
-    const int64_t T = c->T, d = c->d_model, f = c->d_ff, E = c->E;
-    const int64_t nd = expert_numel(c, d), nf = expert_numel(c, f);
+    const Num T = c->T, d = c->d_model, f = c->d_ff, E = c->E;
+    const Num nd = expert_numel(c, d), nf = expert_numel(c, f);
     const size_t need = g_abi.workspace_bytes(c, MOE_CALL_BWD_DW);
     const void* x = ptr(a[1], "x", dt, T * d, T == 0);
     const float* dl = (const float*)ptr(a[2], "dlogits", kF32, T * E);
@@ -328,7 +348,7 @@ struct Item {
 };
 // The pointer of d[name], checked.  The mapping keeps the tensor alive.
 template <typename T>
-void item(T*& out, PyObject* d, const char* name, at::ScalarType type, int64_t numel) {
+void item(T*& out, PyObject* d, const char* name, at::ScalarType type, Num numel) {
   Item it(d, name);
   out = (T*)ptr(it.o, name, type, numel);
 }
@@ -338,12 +358,14 @@ ENTRY(block_chunked) {
   return entry(n, 12, [&] {
     Struct<moe_block_cfg> c(a[0]);
     const moe_cfg* m = &c->moe;
-    const int passes = (int)PyLong_AsLong(a[8]), chunks = (int)PyLong_AsLong(a[9]);
+    // The C ABI takes the low 32 bits; the size of `fill` is checked for the number as given.
+    const int passes = (int)PyLong_AsUnsignedLongMask(a[8]), chunks = (int)PyLong_AsUnsignedLongMask(a[9]);
     if (PyErr_Occurred()) throw Error();
+    const Num given = big(a[9]);
     const bool fwd = passes & MOE_BLOCK_FWD, bwd = passes & MOE_BLOCK_BWD;
-    const int64_t T = m->T, d = m->d_model, f = m->d_ff, E = m->E, k = m->k;
-    const int64_t nd = expert_numel(m, d), nf = expert_numel(m, f), nw = E * f * d;
-    const int64_t st = (int64_t)c->B * c->heads * ((c->S + 63) / 64 * 64);
+    const Num T = m->T, d = m->d_model, f = m->d_ff, E = m->E, k = m->k;
+    const Num nd = expert_numel(m, d), nf = expert_numel(m, f), nw = E * f * d;
+    const Num st = (Num)c->B * c->heads * (((Num)c->S + 63) / 64 * 64);
     moe_block_weights W;
     PyObject* w = a[1];
     item(W.ln1_g, w, "ln1_g", kBf16, d);
@@ -384,7 +406,7 @@ ENTRY(block_chunked) {
     item(A.idx, q, "idx", kI32, T * k);
     item(A.w, q, "w", kF32, T * k);
     item(A.slot, q, "slot", kI32, T * k);
-    item(A.fill, q, "fill", kI32, chunks * E);
+    item(A.fill, q, "fill", kI32, given * E);
     item(A.send_buf, q, "send_buf", kBf16, nd);
     item(A.H, q, "H", kBf16, nf);
     item(A.A, q, "A", kBf16, nf);

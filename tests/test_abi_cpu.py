@@ -111,6 +111,36 @@ def test_binding_rejects_host_tensors_and_short_buffers():
         L.moe_gate_topk(c, torch.zeros(4, 8, dtype=torch.bfloat16), None, None, None, None, None, stream=0)
 
 
+def _fake_device():
+    """Tensors without memory that say they are on the device: the checks come before any use."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    return FakeTensorMode()
+
+
+def test_binding_sizes_do_not_wrap():
+    """A count past 64 bits (4 x (2^31 - 8)^2 wraps to a negative one) is refused like any other."""
+    import torch
+    with _fake_device():
+        t = torch.empty(16, device="cuda")
+    n = 2 ** 31 - 8
+    c = L.make_cfg(4, n, n, 4, 1, 1, dtype="f32")
+    with pytest.raises(ValueError, match=f"the call touches {4 * n * n}"):
+        L.moe_pack_weights(c, t, t, t, t, stream=0)
+
+
+@pytest.mark.filterwarnings("ignore")
+def test_binding_refuses_partitions_past_32_bits():
+    import torch
+    c = L.make_block_cfg(2, 64, 2, 512, 8, 2, 40)
+    with _fake_device():
+        b = L.alloc_block(c, 1)
+        w = {n: torch.empty(m, dtype=dt, device="cuda") for n, (m, dt) in L.block_shapes(c, 1).items()}
+        x = torch.empty(c.moe.T * c.moe.d_model, dtype=torch.bfloat16, device="cuda")
+    for n in (2 ** 32 + 1, 2 ** 70 + 1):
+        with pytest.raises(ValueError, match="fill has 8 elements"):
+            L.moe_block_chunked(c, w, b, x, x, x, x, b, 1, n, [0, 0, 0], b["ws"])
+
+
 def test_isa_check_flags_use_before_wait():
     from paper_2404_19429_amd.isa_check import check_text
     clean = """_ZN4lmoe16gemm_wide_kernelX:
