@@ -138,12 +138,18 @@ void* stream_arg(PyObject* o) {
   return s;
 }
 
+// The C call without the interpreter lock, which is held again however it ends.
 template <typename F>
 PyObject* status(F&& call) {
+  struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+  };
   moe_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = call();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked u;
+    st = call();
+  }
   return PyLong_FromLong(st);
 }
 

@@ -3,6 +3,8 @@ header declares, and rejects invalid arguments on the host before launching."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -126,6 +128,39 @@ def test_binding_sizes_do_not_wrap():
     c = L.make_cfg(4, n, n, 4, 1, 1, dtype="f32")
     with pytest.raises(ValueError, match=f"the call touches {4 * n * n}"):
         L.moe_pack_weights(c, t, t, t, t, stream=0)
+
+
+_THROWING = """
+#include <new>
+extern "C" int thrower() { throw std::bad_alloc(); }
+"""
+
+
+def test_binding_turns_a_c_exception_into_a_python_one(tmp_path):
+    """An exception from the library (say, out of host memory) reaches Python with
+    the interpreter lock held.  In a child process: without the lock it would end it."""
+    src, lib = tmp_path / "t.cpp", tmp_path / "t.so"
+    src.write_text(_THROWING)
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    code = f"""
+import ctypes, torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2404_19429_amd import lancet_moe as L, _bind
+addr = ctypes.cast(ctypes.CDLL({str(lib)!r}).thrower, ctypes.c_void_p).value
+_bind.init({{n: addr for n in L.EXPORTS}}, lambda s: 0, L.moe_cfg, L.moe_block_cfg)
+with FakeTensorMode():
+    f, i = (torch.empty(0, dtype=t, device="cuda") for t in (torch.float32, torch.int32))
+for _ in range(3):
+    try:
+        L.moe_gate_topk(L.moe_cfg(), f, f, None, f, i, f)
+    except RuntimeError as e:
+        assert "bad_alloc" in str(e), e
+    else:
+        raise SystemExit("no exception")
+print("raised")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "raised" in r.stdout, (r.returncode, r.stdout, r.stderr[-2000:])
 
 
 @pytest.mark.filterwarnings("ignore")
