@@ -330,13 +330,18 @@ size_t dispatch_ws_bytes(const moe_cfg& c) {
 static void dispatch_walk(const moe_cfg& c, const void* x, const int32_t* idx, const int32_t* perm,
                           const int32_t* carry, int32_t* fill, int32_t* slot, void* send_buf, void* ws, hipStream_t s) {
   const int64_t nch = (c.T + kRouteChunk - 1) / kRouteChunk;
-  if (nch == 1) {   // one launch instead of two or three (48 tokens of d 1024: 3.9 + 5.7 -> 5.7 us)
+  // One chunk: one launch instead of two or three (48 tokens of d 1024: 3.9 + 5.7
+  // -> 5.7 us), unless its blocks, each of which ranks the chunk in a time that
+  // grows with k, are so many that the ranks cost more than the launches: blocks x
+  // k is below 16 per CU.  256 tokens of d 8192, one launch against the general
+  // ones: k = 2 (8 per CU) 7.9 and 9.2 us, k = 4 (16) 13.9 and 12.2; of d 4096, k =
+  // 4 (8) 9.7 and 11.0, k = 8 (16) 21.0 and 19.7.
+  const int64_t sb = (c.T * (c.d_model / (c.dtype == MOE_BF16 ? 8 : 4)) + kRouteChunk - 1) / kRouteChunk;
+  if (nch == 1 && sb * c.k < (int64_t)16 * num_cus()) {
     auto go = [&](auto tag) {
       using T = decltype(tag);
-      const int64_t n = c.T * (c.d_model / Vec<T>::N);
-      hipLaunchKernelGGL(dispatch_small_kernel<T>, dim3((unsigned)((n + kRouteChunk - 1) / kRouteChunk)),
-                         dim3(kRouteChunk), 0, s, (const T*)x, idx, perm, carry, fill, slot, (T*)send_buf, (int)c.T,
-                         c.d_model, c.E, c.k, c.C);
+      hipLaunchKernelGGL(dispatch_small_kernel<T>, dim3((unsigned)sb), dim3(kRouteChunk), 0, s, (const T*)x, idx, perm,
+                         carry, fill, slot, (T*)send_buf, (int)c.T, c.d_model, c.E, c.k, c.C);
     };
     if (c.dtype == MOE_BF16) go(uint16_t{});
     else go(float{});
