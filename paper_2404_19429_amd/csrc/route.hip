@@ -209,7 +209,7 @@ __global__ __launch_bounds__(64) void route_scan_kernel(const int32_t* __restric
 // slot[t][r] = base[chunk][e] + rank (or -1 past the capacity), and
 // send_buf[e][slot][:] = x[t][:] for every kept (t, r).
 // perm as in route_rank_kernel: the thread's positions j hold tokens perm[j].
-// nfused > 0 (at most 64 chunks with wave-uniform tokens, 8 without): the chunk
+// nfused > 0 (at most 64 chunks with wave-uniform tokens, a few without): the chunk
 // bases are not read from `base` but summed here from the chunk counts (one wave
 // reduction, or a few loads, per token and choice; the scan launch is skipped), and the first
 // wave of block b writes fill[e] = min(C, carry_e + all counts of e) for
@@ -352,12 +352,15 @@ static void dispatch_walk(const moe_cfg& c, const void* x, const int32_t* idx, c
   int32_t* rank = base + nch * c.E;
   // The copy launch sums the chunk bases itself when its waves are token-uniform
   // (as row_launch decides) and there are at most 64 chunks (one count per
-  // lane), or at most 8 chunks (2048 tokens) otherwise, each lane its own few
-  // loads; else a scan launch (with 128 chunks the in-copy sums cost more than
-  // the launch they save).  2048 tokens of d 768: scan 4.4 + copy 5.3 -> copy 7.7 us.
+  // lane); else a scan launch (with 128 chunks the in-copy sums cost more than
+  // the launch they save).  Otherwise each lane loads the counts of every chunk
+  // before its own for each of its k choices: up to 8 chunks, and chunks x k = 24.  Scan and
+  // copy against the copy alone, 2048 tokens: d 768, k = 2 (16) 4.4 + 5.3 and 7.7
+  // us; whole calls, d 72, k = 3 (24) 10.7 and 10.3, k = 4 (32) 12.2 and 12.4, k = 8
+  // (64) 19.1 and 20.9.
   const int V = c.dtype == MOE_BF16 ? 8 : 4;
   const bool uni = (c.d_model / V) % kWave == 0 && c.T < ((int64_t)1 << 30);
-  const bool fused = nch > 0 && nch <= (uni ? kWave : 8);
+  const bool fused = nch > 0 && (uni ? nch <= kWave : nch <= 8 && nch * c.k <= 24);
   const int nfused = fused ? (int)nch : 0;
   if (nch > 0)
     hipLaunchKernelGGL(route_rank_kernel, dim3((unsigned)nch), dim3(kRouteChunk), 0, s, idx, perm, counts, rank, c.T,

@@ -1,5 +1,5 @@
 """Slot assignment and copy on each of their launch shapes: one chunk of tokens
-(a single launch), up to 8 chunks without wave-uniform rows (no scan launch) and
+(a single launch), a few chunks without wave-uniform rows (no scan launch) and
 more, in token order with a carry and in batch-prioritized order."""
 from __future__ import annotations
 
@@ -32,10 +32,12 @@ def _walk(idx, order, carry, C, E):
     return slot, used
 
 
-# 1 / 255 / 256: one chunk, of d 4096 and 2056 with k = 8 wide enough for the general launches; 257 / 2048 with d 72 (rows are not whole waves): bases
-# summed in the copy; 2049: the scan launch; d 512: wave-uniform rows.
+# 1 / 255 / 256: one chunk, of d 4096 and 2056 with k = 8 wide enough for the
+# general launches; 257 / 2048 with d 72 or 96 (rows are not whole waves): bases
+# summed in the copy up to k = 3; k = 4, 2049: the scan launch; d 512: wave-uniform rows.
 @pytest.mark.parametrize("T,d,E,k,dtype", [(1, 64, 4, 1, "bf16"), (255, 96, 5, 3, "f32"), (256, 512, 64, 2, "bf16"),
                                            (257, 72, 8, 2, "f32"), (2048, 96, 16, 2, "bf16"), (2049, 96, 3, 2, "bf16"),
+                                           (2048, 96, 16, 3, "bf16"), (2048, 72, 16, 4, "f32"),
                                            (700, 512, 8, 2, "bf16"), (256, 4096, 64, 8, "bf16"),
                                            (255, 2056, 32, 8, "f32")])
 def test_dispatch_launch_shapes(L, T, d, E, k, dtype):
