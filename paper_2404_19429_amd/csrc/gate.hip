@@ -149,7 +149,11 @@ __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict
 
   // Top-k by (logit desc, expert asc): four lanes per token scan every fourth
   // expert into sorted lists of KT keys (distinct: the expert is part of the
-  // key), which two exchanges merge, so each lane ends with the token's list.
+  // key), which two exchanges merge, so each lane ends with the token's list.  Of
+  // two sorted lists the larger of best[r] and other[KT - 1 - r] are the KT largest
+  // keys, falling and then rising, which log2 KT rounds of exchanges sort: 20
+  // comparisons for KT = 8 where inserting one by one takes 64 (1000 tokens, d 256,
+  // 8 experts, k = 8 8.4 -> 6.9 us; k = 1 and 2 are the same).
   const int tl = threadIdx.x >> 2, l4 = threadIdx.x & 3;
   if (tl < ntok) {
     uint64_t best[KT];
@@ -171,7 +175,16 @@ __global__ __launch_bounds__(64 * NWV) void gate_topk_kernel(const T* __restrict
 #pragma unroll
       for (int r = 0; r < KT; ++r) other[r] = __shfl_xor(best[r], o, kWave);
 #pragma unroll
-      for (int r = 0; r < KT; ++r) insert(other[r]);
+      for (int r = 0; r < KT; ++r) best[r] = best[r] > other[KT - 1 - r] ? best[r] : other[KT - 1 - r];
+#pragma unroll
+      for (int h = KT / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int r = 0; r < KT; ++r)
+          if ((r & h) == 0) {
+            const uint64_t lo = best[r] < best[r + h] ? best[r] : best[r + h];
+            best[r] = best[r] < best[r + h] ? best[r + h] : best[r];
+            best[r + h] = lo;
+          }
     }
     const float m = float_from_order_key((uint32_t)(best[0] >> 32));
     float ex[KT], denom = 0.f;

@@ -25,7 +25,7 @@ def L():
 @pytest.mark.parametrize("T", [1, 37, 16391])
 @pytest.mark.parametrize("E,k,renorm,dtype", [(1, 1, 0, "f32"), (3, 1, 0, "bf16"), (3, 3, 1, "f32"), (16, 2, 1, "bf16"),
                                               (17, 4, 0, "bf16"), (33, 5, 1, "bf16"), (48, 3, 0, "f32"),
-                                              (64, 8, 1, "bf16")])
+                                              (64, 8, 1, "bf16"), (9, 7, 1, "bf16"), (8, 8, 0, "f32")])
 def test_gate_launch_shapes(L, T, E, k, renorm, dtype):
     """Logits within an ulp of the float64 ones; the choices are those of the
     kernel's own logits.  A weight is a quotient of float sums of at most E
