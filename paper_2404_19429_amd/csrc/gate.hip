@@ -217,17 +217,20 @@ static void launch_gate_k(const moe_cfg& c, const void* x, const void* Wg, const
   hipLaunchKernelGGL((gate_topk_kernel<T, MT, NT, NWV, KT>), dim3((unsigned)blocks), dim3(64 * NWV), 0, s,
                      (const T*)x, (const T*)Wg, bias, logits, idx, w, c.T, c.d_model, c.E, c.k, c.renorm);
 }
-// 32 tokens per block; 16 where 32 would leave fewer than two blocks per CU (the
+// 32 tokens per block; 16 where that gives the CUs at most three blocks each (the
 // kernel is then latency: loads, a short MFMA chain, the sums, the selection).
 // One MI355X, with the wave sums spread over the block and four lanes per token
 // selecting (before: one wave summing, one lane per token with a list of eight):
 // 2048 tokens, d 768, 8 experts 11.3 -> 6.2 us; 8192 tokens, d 1024, 32 experts
 // 22.5 -> 16.3; 32768 tokens, 64 experts 123 -> 101; 16384 tokens, d 2048, 8
-// experts 28.6 -> 28.0 (fp64 matrix rate).
+// experts 28.6 -> 28.0 (fp64 matrix rate).  The line, 16- against 32-token blocks:
+// 12000 tokens, d 4096, float, 24 experts 67 and 81 us, 64 experts 140 and 158; of
+// 16000 tokens, where both are whole rounds and the smaller block reads Wg twice
+// as often, 88 and 79, 187 and 160 (bf16 164 and 153).
 template <typename T, int NT, int NWV, int KT>
 static void launch_gate_m(const moe_cfg& c, const void* x, const void* Wg, const float* bias, float* logits,
                           int32_t* idx, float* w, hipStream_t s) {
-  if (c.T < (int64_t)32 * 2 * num_cus()) launch_gate_k<T, 1, NT, NWV, KT>(c, x, Wg, bias, logits, idx, w, s);
+  if (c.T <= (int64_t)16 * 3 * num_cus()) launch_gate_k<T, 1, NT, NWV, KT>(c, x, Wg, bias, logits, idx, w, s);
   else launch_gate_k<T, 2, NT, NWV, KT>(c, x, Wg, bias, logits, idx, w, s);
 }
 // KT: the top-k list's length, k rounded up to 1, 2, 4 or 8.

@@ -21,7 +21,7 @@ def L():
     return lancet_moe
 
 
-# 16384 tokens and more take 32-token blocks on 256 CUs; 16391 and 37 end inside a block.
+# More than 12288 tokens take 32-token blocks on 256 CUs; 16391 and 37 end inside a block.
 @pytest.mark.parametrize("T", [1, 37, 16391])
 @pytest.mark.parametrize("E,k,renorm,dtype", [(1, 1, 0, "f32"), (3, 1, 0, "bf16"), (3, 3, 1, "f32"), (16, 2, 1, "bf16"),
                                               (17, 4, 0, "bf16"), (33, 5, 1, "bf16"), (48, 3, 0, "f32"),
