@@ -248,50 +248,56 @@ size_t expert_sk_ws_bytes(const moe_cfg& c) { return c.dtype == MOE_BF16 ? (size
 // experts, no K-split) 372 -> 328, of 6000 tokens (d 1536, 32 experts) 178 -> 145;
 // of 16384 tokens (8 experts) 256-tiles stay, 948 against 971.
 struct TileCost {
-  int bm, bn, slots;
+  int bm, bn, per_cu;   // per_cu: blocks of this shape on a CU, so a round is per_cu tiles per CU
   double full, part, store;
   void (*run)(const WideCall&, hipStream_t);
 };
-static const TileCost kTilesM[] = {{256, 256, 256, 650., 650., 8000., run_wide_256x256},
-                                   {192, 256, 256, 560., 560., 7000., run_wide_192x256},
-                                   {128, 128, 512, 520., 330., 4500., run_wide_128x128},
-                                   {64, 128, 512, 390., 230., 3000., run_wide_64x128},
-                                   {64, 64, 512, 300., 190., 2000., run_wide_64x64}};
-static double tile_cost(const TileCost& t, const WideCall& w) {
+static const TileCost kTilesM[] = {{256, 256, 1, 650., 650., 8000., run_wide_256x256},
+                                   {192, 256, 1, 560., 560., 7000., run_wide_192x256},
+                                   {128, 128, 2, 520., 330., 4500., run_wide_128x128},
+                                   {64, 128, 2, 390., 230., 3000., run_wide_64x128},
+                                   {64, 64, 2, 300., 190., 2000., run_wide_64x64}};
+static double tile_cost(const TileCost& t, const WideCall& w, int cus) {
   // M-tiles of a group: a mean over the routed rows' spread.
   const double tm = 0.25 * std::ceil(std::max(1., w.expect - w.spread) / t.bm) + 0.5 * std::ceil(w.expect / t.bm) +
                     0.25 * std::ceil((w.expect + w.spread) / t.bm);
   const double tiles = std::ceil(w.groups * tm * std::ceil((double)w.cols / t.bn));
-  const double rounds = std::floor(tiles / t.slots), rem = tiles - rounds * t.slots;
+  const double slots = (double)t.per_cu * cus;
+  const double rounds = std::floor(tiles / slots), rem = tiles - rounds * slots;
   const double steps = w.p.K / 32., store = w.kind == WK_FWD1 || w.kind == WK_DACT ? t.store : t.store / 2;
-  double last = rem <= 0 ? 0. : steps * (rem <= 256 ? t.part : t.full) + store;
+  double last = rem <= 0 ? 0. : steps * (rem <= cus ? t.part : t.full) + store;
   // A K-split last round: its share of a round, and the partial tiles' write and sum.
-  if (t.bm == 256 && w.p.ksplit && (w.kind == WK_NK || w.kind == WK_KN) && rounds > 0 && rem > 0 && 4 * rem <= t.slots)
-    last = steps * t.full * rem / t.slots + 15000.;
+  if (t.bm == 256 && w.p.ksplit && (w.kind == WK_NK || w.kind == WK_KN) && rounds > 0 && rem > 0 && 4 * rem <= slots)
+    last = steps * t.full * rem / slots + 15000.;
   return rounds * (steps * t.full + store) + last;
+}
+// The tile of a ragged-M product (index into kTilesM).
+static int tile_m(const WideCall& w, int cus) {
+  int best = 0;
+  for (int i = 1; i < (int)(sizeof kTilesM / sizeof kTilesM[0]); ++i)
+    if (tile_cost(kTilesM[i], w, cus) < tile_cost(kTilesM[best], w, cus)) best = i;
+  return best;
+}
+// The tile of a ragged-K product, 256 (true) or 128 wide: 128-tiles where 256-tiles
+// would not make two rounds (dW of 2048 tokens, d 768, 8 experts, 288 large tiles:
+// 43 -> 32 us; of 20000 tokens, d 512, 128 large tiles: 82 -> 57); with more the
+// larger tile wins (8192 tokens, d 1024, 16 experts, 1024 large tiles: 142 against 166).
+// Groups known to be equally long and not short (w.expect, the dense weight
+// gradients' token ranges): whole rounds decide, 256-tiles one per CU, 128-tiles
+// three per CU (192 large tiles' work on 256 CUs) in 3/4 of the time.  dW of 256 large
+// tiles and 8192 rows each, 128- against 256-tiles (two launches) 645 and 505 us, of
+// 416 tiles and 1260 rows 191 and 170; of 512 tiles and 75 rows 45 and 50.  Routed
+// groups may be skewed, which the smaller tile spreads better.
+static bool large_tile_k(const WideCall& w, int cus) {
+  const int64_t large = (w.rows + 255) / 256 * ((w.cols + 255) / 256) * w.groups;
+  const int64_t three = cus * 3 / 4;
+  if (large > 2 * cus) return true;
+  return w.kind == WK_WGF32 && w.expect >= 512. && 3 * ((large + three - 1) / three) >= 4 * ((large + cus - 1) / cus);
 }
 static void run_wide_any(const WideCall& w, hipStream_t s) {
   if (w.rows <= 0 || w.cols <= 0 || w.groups <= 0) return;
-  if (w.kind >= WK_DW) {
-    // Ragged-K: 128-tiles where 256-tiles would not make two rounds (dW of 2048
-    // tokens, d 768, 8 experts, 288 large tiles: 43 -> 32 us; of 20000 tokens,
-    // d 512, 128 large tiles: 82 -> 57); with more the larger tile wins (8192
-    // tokens, d 1024, 16 experts, 1024 large tiles: 142 against 166).
-    // Groups known to be equally long and not short (w.expect, the dense weight
-    // gradients' token ranges): whole rounds decide, 256-tiles one per CU, 128-tiles
-    // three per CU (192 large tiles' work) in 3/4 of the time.  dW of 256 large tiles
-    // and 8192 rows each, 128- against 256-tiles (two launches) 645 and 505 us, of 416
-    // tiles and 1260 rows 191 and 170; of 512 tiles and 75 rows 45 and 50.  Routed
-    // groups may be skewed, which the smaller tile spreads better.
-    const int64_t large = (w.rows + 255) / 256 * ((w.cols + 255) / 256) * w.groups;
-    const bool small = w.kind == WK_WGF32 && w.expect >= 512. ? 3 * ((large + 191) / 192) < 4 * ((large + 255) / 256)
-                                                              : true;
-    return small && large <= 512 ? run_wide_128x128(w, s) : run_wide_256x256(w, s);
-  }
-  const TileCost* best = &kTilesM[0];
-  for (const TileCost& t : kTilesM)
-    if (tile_cost(t, w) < tile_cost(*best, w)) best = &t;
-  best->run(w, s);
+  if (w.kind >= WK_DW) return large_tile_k(w, num_cus()) ? run_wide_256x256(w, s) : run_wide_128x128(w, s);
+  kTilesM[tile_m(w, num_cus())].run(w, s);
 }
 
 // Expert products.  bf16: blocked operands, wide tiles; outputs that a later
@@ -300,14 +306,20 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
 // kernel, row-major.
 // rows: rows of the output per group (ragged-M: the capacity C, with up to 15
 // alignment rows; ragged-K: M); cols: N.
+//
+// Rows a group is expected to hold, and their standard deviation: the call's
+// assignments spread evenly (T is only a hint here: rows may come from elsewhere).
+static WideCall expert_call(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, bool later) {
+  const double expect = c.T > 0 ? std::min<double>(c.C, (double)c.T * c.k / c.E) : c.C;
+  const double spread = std::sqrt(expect * (1. - (double)c.k / c.E));
+  // A later partition's rows start anywhere in a 16-row block.
+  return WideCall{kind, c.act, c.E, rows, cols, expect + (later ? 7.5 : 0.), spread, p};
+}
 template <bool B_K, bool RAGGED_K, int EPI>
 static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s,
                        bool later = false) {
   if (rows <= 0 || cols <= 0 || c.E <= 0) return;
-  // Rows a group is expected to hold: the call's assignments spread evenly (T is
-  // only a hint here: rows may come from elsewhere).
-  const double expect = c.T > 0 ? std::min<double>(c.C, (double)c.T * c.k / c.E) : c.C;
-  const double spread = std::sqrt(expect * (1. - (double)c.k / c.E));
+  const WideCall w = expert_call(c, kind, p, rows, cols, later);
   if (c.dtype != MOE_BF16) {
     // The tile whose busiest CU has the least work: tiles per CU times area, the
     // 32-tile's extra loads per flop counted as 30 %.
@@ -316,7 +328,8 @@ static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int
     // f 1280, 8 experts) 15 and 23, its H 24 and 15.
     auto cost = [&](int t, double f) {
       const double n = RAGGED_K ? std::ceil((double)rows / t)
-                                : 0.5 * (std::ceil(std::max(1., expect - spread) / t) + std::ceil((expect + spread) / t));
+                                : 0.5 * (std::ceil(std::max(1., w.expect - w.spread) / t) +
+                                         std::ceil((w.expect + w.spread) / t));
       return std::ceil(c.E * n * std::ceil((double)cols / t) / num_cus()) * t * t * f;
     };
     const bool fits = (double)c.E * ((rows + 46) / 32) * ((cols + 31) / 32) <= 1 << 22;   // bounds the grid
@@ -324,10 +337,8 @@ static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int
     else launch_f32<2, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
     return;
   }
-  // A later partition's rows start anywhere in a 16-row block.
-  run_wide_any(WideCall{kind, c.act, c.E, rows, cols, expect + (later ? 7.5 : 0.), spread, p}, s);
+  run_wide_any(w, s);
 }
-
 // Rows per expert block of an [E][C][*] buffer (C rounded up to 16 for bf16).
 static int64_t rows_alloc(const moe_cfg& c) { return c.dtype == MOE_BF16 ? pad16(c.C) : c.C; }
 
@@ -546,6 +557,28 @@ void launch_dense_wide(int64_t M, int N, int K, const void* A, const void* B, bo
                0, N, K, 0, (int)M};
   p.ksplit = 0;
   run_wide_any(WideCall{b_nk ? (resid ? WK_NK_RES : WK_NK) : WK_KN, MOE_ACT_IDENTITY, 1, M, N, (double)M, 0., p}, s);
+}
+
+// The tile, (rows << 16) + columns, that the choice above gives a bf16 expert
+// product (kProd*) of a call, or a dense product, on `cus` compute units.
+int expert_tile(const moe_cfg& c, int product, bool later, int cus) {
+  static const WideKind kinds[kProducts] = {WK_FWD1, WK_NK, WK_DACT, WK_KN, WK_DW, WK_DW};
+  const bool to_f = product == kProdFwd1 || product == kProdDA || product == kProdDW2;   // N = f (else d)
+  GemmParams p{};
+  p.K = to_f ? c.d_model : c.d_ff;
+  p.ksplit = c.ksplit;
+  const bool dw = product == kProdDW2 || product == kProdDW1;
+  const WideCall w = expert_call(c, kinds[product], p, dw ? (to_f ? c.d_model : c.d_ff) : c.C,
+                                 to_f ? c.d_ff : c.d_model, later);
+  if (dw) return large_tile_k(w, cus) ? (256 << 16) + 256 : (128 << 16) + 128;
+  const TileCost& t = kTilesM[tile_m(w, cus)];
+  return (t.bm << 16) + t.bn;
+}
+int dense_tile(int64_t M, int N, int K, int cus) {
+  GemmParams p{};
+  p.K = K;
+  const TileCost& t = kTilesM[tile_m(WideCall{WK_NK, MOE_ACT_IDENTITY, 1, M, N, (double)M, 0., p}, cus)];
+  return (t.bm << 16) + t.bn;
 }
 
 }  // namespace lmoe
