@@ -278,26 +278,64 @@ static int tile_m(const WideCall& w, int cus) {
     if (tile_cost(kTilesM[i], w, cus) < tile_cost(kTilesM[best], w, cus)) best = i;
   return best;
 }
-// The tile of a ragged-K product, 256 (true) or 128 wide: 128-tiles where 256-tiles
-// would not make two rounds (dW of 2048 tokens, d 768, 8 experts, 288 large tiles:
-// 43 -> 32 us; of 20000 tokens, d 512, 128 large tiles: 82 -> 57); with more the
-// larger tile wins (8192 tokens, d 1024, 16 experts, 1024 large tiles: 142 against 166).
-// Groups known to be equally long and not short (w.expect, the dense weight
-// gradients' token ranges): whole rounds decide, 256-tiles one per CU, 128-tiles
-// three per CU (192 large tiles' work on 256 CUs) in 3/4 of the time.  dW of 256 large
-// tiles and 8192 rows each, 128- against 256-tiles (two launches) 645 and 505 us, of
-// 416 tiles and 1260 rows 191 and 170; of 512 tiles and 75 rows 45 and 50.  Routed
-// groups may be skewed, which the smaller tile spreads better.
-static bool large_tile_k(const WideCall& w, int cus) {
-  const int64_t large = (w.rows + 255) / 256 * ((w.cols + 255) / 256) * w.groups;
-  const int64_t three = cus * 3 / 4;
-  if (large > 2 * cus) return true;
-  return w.kind == WK_WGF32 && w.expect >= 512. && 3 * ((large + three - 1) / three) >= 4 * ((large + cus - 1) / cus);
+// The tile of a ragged-K product: 128 or 256 wide.  A tile is as long as its group
+// and its blocks stay on the CUs, so whole rounds decide: 256-tiles one per CU,
+// 128-tiles three.  Modelled, in ns per 32 rows of a group: a round of 256-tiles 720
+// to half full, 900 full; of 128-tiles 440 at one per CU, 620 at two, 850 at three;
+// 4000 and 2000 for a round's stores, 8000 and 7000 once.  Below 512 rows per group
+// the choice is worth 2 us at most, and 128-tiles run.
+//
+// Measured on one MI355X, one product, 128- against 256-tiles: 128 large tiles of
+// 2048 rows (d 512, f 2048, 8 experts) 46 and 57 us; 192 (d 768) of 512 rows 25 and
+// 27, of 4096 132 and 119; 240 (d 640, f 1280, 16 experts) of 2048 122 and 81; 256 (d
+// 1024) of 200 20 and 19, of 1024 50 and 41, of 8192 343 and 239; 288 (d 768, f 3072)
+// of 512 34 and 38, of 8192 387 and 405; 384 of 512 39 and 40, of 8192 449 and 409;
+// 512 of 1024 88 and 73.  Past two rounds of 256-tiles they win or tie at any length.
+//
+// Routed groups may be skewed, which shows on the device only; there the longest
+// group's tiles are the time, and smaller ones share them between CUs (Zipf 1.2,
+// capacity twice the mean of 4096 rows: 256 large tiles of 8 experts 152 and 191 us,
+// of 64 experts 174 and 194; 512 large tiles 239 and 245, of 1024 rows 72 and 74).  So
+// up to one and a half rounds, and where an idle launch (3 us) is little, both
+// shapes are launched and the row counts pick the one that runs.
+// The dense weight gradients' groups are token ranges of one length (w.expect): where
+// they are not short, 128-tiles take 3/4 of the time of a 256-tile round for the work
+// of 192 large tiles.  dW of 256 large tiles and 8192 rows each, 128- against
+// 256-tiles (two launches) 645 and 505 us, of 416 tiles and 1260 rows 191 and 170; of
+// 512 tiles and 75 rows 45 and 50.
+enum TileK { kTileK128, kTileK256, kTileKByRows };
+static TileK tile_k(const WideCall& w, int cus) {
+  const auto tiles = [&](int t) { return (w.rows + t - 1) / t * ((w.cols + t - 1) / t) * w.groups; };
+  const int64_t large = tiles(256);
+  if (large > 2 * cus) return kTileK256;
+  if (w.kind == WK_WGF32) {
+    const int64_t three = cus * 3 / 4;
+    return w.expect >= 512. && 3 * ((large + three - 1) / three) >= 4 * ((large + cus - 1) / cus) ? kTileK256
+                                                                                                  : kTileK128;
+  }
+  if (w.expect < 512.) return kTileK128;
+  const double steps = w.expect / 32.;
+  // rounds of `per` tiles: full ones, and the last by its share per CU
+  auto cost = [&](int64_t n, int64_t per, double full, double store, auto part) {
+    const int64_t rounds = n / per, rem = n % per;
+    return rounds * (steps * full + store) + (rem ? steps * part((double)rem / cus) + store : 0.);
+  };
+  const double c256 = 8000. + cost(large, cus, 900., 4000., [](double r) { return r <= 0.5 ? 720. : 540. + 360. * r; });
+  const double c128 = 7000. + cost(tiles(128), 3 * cus, 850., 2000., [](double r) {
+    return r <= 1. ? 440. : r <= 2. ? 260. + 180. * r : 160. + 230. * r;
+  });
+  if (c128 <= c256) return kTileK128;
+  return 2 * large <= 3 * cus ? kTileKByRows : kTileK256;
 }
 static void run_wide_any(const WideCall& w, hipStream_t s) {
   if (w.rows <= 0 || w.cols <= 0 || w.groups <= 0) return;
-  if (w.kind >= WK_DW) return large_tile_k(w, num_cus()) ? run_wide_256x256(w, s) : run_wide_128x128(w, s);
-  kTilesM[tile_m(w, num_cus())].run(w, s);
+  if (w.kind < WK_DW) return kTilesM[tile_m(w, num_cus())].run(w, s);
+  const TileK t = tile_k(w, num_cus());
+  WideCall q = w;
+  q.p.only = t == kTileKByRows ? 1 : 0;
+  if (t != kTileK128) run_wide_256x256(q, s);
+  q.p.only = t == kTileKByRows ? 2 : 0;
+  if (t != kTileK256) run_wide_128x128(q, s);
 }
 
 // Expert products.  bf16: blocked operands, wide tiles; outputs that a later
@@ -560,7 +598,8 @@ void launch_dense_wide(int64_t M, int N, int K, const void* A, const void* B, bo
 }
 
 // The tile, (rows << 16) + columns, that the choice above gives a bf16 expert
-// product (kProd*) of a call, or a dense product, on `cus` compute units.
+// product (kProd*) of a call, or a dense product, on `cus` compute units (0: by the
+// row counts).
 int expert_tile(const moe_cfg& c, int product, bool later, int cus) {
   static const WideKind kinds[kProducts] = {WK_FWD1, WK_NK, WK_DACT, WK_KN, WK_DW, WK_DW};
   const bool to_f = product == kProdFwd1 || product == kProdDA || product == kProdDW2;   // N = f (else d)
@@ -570,7 +609,10 @@ int expert_tile(const moe_cfg& c, int product, bool later, int cus) {
   const bool dw = product == kProdDW2 || product == kProdDW1;
   const WideCall w = expert_call(c, kinds[product], p, dw ? (to_f ? c.d_model : c.d_ff) : c.C,
                                  to_f ? c.d_ff : c.d_model, later);
-  if (dw) return large_tile_k(w, cus) ? (256 << 16) + 256 : (128 << 16) + 128;
+  if (dw) {
+    const TileK t = tile_k(w, cus);
+    return t == kTileKByRows ? 0 : t == kTileK256 ? (256 << 16) + 256 : (128 << 16) + 128;
+  }
   const TileCost& t = kTilesM[tile_m(w, cus)];
   return (t.bm << 16) + t.bn;
 }

@@ -33,6 +33,7 @@ struct GemmParams {
   float* part;      // wide ragged-M products: partial tiles of the K-split (stream-K) schedule
   int ksplit;       // wide plain-store ragged-M products: 1 = a short last round may be K-split
   int kchunk;       // rb == re == NULL and kchunk > 0: group g's rows are [g kchunk, (g + 1) kchunk)
+  int only;         // ragged-K: 1 = run only if the groups are even, 2 = only if they are skewed, 0 = always
 };
 
 // Row range of group g, clamped to the buffer so bad ranges cannot reach outside it.
@@ -599,6 +600,22 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
   // The K-split products place their short tiles last (SEP), so the split
   // round holds the short tiles, whose partial sums stop at the group's rows.
   constexpr bool SPLIT = TC::KSPLIT && !RAGGED_K && EPI == EPI_STORE;
+  if constexpr (RAGGED_K && EPI != EPI_WGF32) {
+    // A product launched on two tile shapes: the row counts say which one runs
+    // (skewed: the longest group has at least 1.5 times the mean of all).
+    if (p.only != 0) {
+      int lo = 0, span = 0;
+      if (lane < groups) group_rows(p, lane, lo, span);
+      int most = span, all = span;   // (64 groups of less than 2^24 rows)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        most = max(most, __shfl_xor(most, o, kWave));
+        all += __shfl_xor(all, o, kWave);
+      }
+      const bool skewed = 2 * (int64_t)most * groups >= 3 * (int64_t)all;
+      if (__builtin_amdgcn_readfirstlane((int)skewed) != (p.only == 2 ? 1 : 0)) return;
+    }
+  }
   const WPrefix P = wide_tile_prefix<BMT, RAGGED_K, SPLIT>(p, lane, groups, tilesM, tilesN);
   const int total = P.NF + P.NP;
   if constexpr (RAGGED_K) {

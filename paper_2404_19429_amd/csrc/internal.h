@@ -99,7 +99,8 @@ void launch_expert_bwd_dx(const moe_cfg& c, const void* dO, const int32_t* rb, c
 void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const void* dO, const void* dH,
                           const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s);
 // The tile, (rows << 16) + columns, of a bf16 expert product (kProd*; later as
-// above) or a dense product on a device of `cus` compute units.
+// above) or a dense product on a device of `cus` compute units; 0 where the row
+// counts decide on the device.
 int expert_tile(const moe_cfg& c, int product, bool later, int cus);
 int dense_tile(int64_t M, int N, int K, int cus);
 // Per-product timing of the expert products on this thread (moe_product_timing):

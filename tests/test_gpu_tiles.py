@@ -15,6 +15,7 @@ import pytest
 
 from synth import LayerSpec, layer_inputs
 from tests.gpu_harness import ebuf, host, kept_rows, log, nan_fill, run_layer, spec_C, to_dev
+from tests.tile_choice import expert_tile
 
 pytestmark = pytest.mark.gpu
 
@@ -82,14 +83,10 @@ def test_partitions_on_smaller_tiles_are_bitwise_the_whole_batch(L, case):
         np.testing.assert_array_equal(host(getattr(b, name)), host(getattr(whole, name)), err_msg=name)
 
 
-@pytest.mark.parametrize("T,d,f,E,k", [(37, 64, 192, 4, 2), (300, 320, 192, 2, 2), (1100, 1088, 2112, 16, 2)],
-                         ids=["few_rows", "column_remainders", "more_than_512_large_tiles"])
-def test_weight_gradients_on_both_tile_shapes(L, T, d, f, E, k):
+def _check_weight_gradients(b, E):
     """dW2 = dO^T A and dW1 = dH^T X against float32 products of the kernel's own
     bf16 inputs: two float sums of n terms (each within gamma_n sum|a||b|, u =
     2^-24) and one bf16 rounding (half an ulp, 2^-8 of the value)."""
-    spec = _s(T, d, f, E, k)
-    b, _ = run_layer(L, spec, layer_inputs(spec), spec_C(spec))
     fill = host(b.fill)
     bufs = {n: ebuf(b, n) for n in ("dO", "A", "dH", "send_buf")}
     for e in range(E):
@@ -100,3 +97,25 @@ def test_weight_gradients_on_both_tile_shapes(L, T, d, f, E, k):
             got = getattr(b, name)[e].double()
             bound = 2 * n * 2.0 ** -24 * mag + 2.0 ** -8 * ref.abs()
             assert bool(((got - ref).abs() <= bound + 1e-30).all()), f"{name} of expert {e}"
+    return fill
+
+
+@pytest.mark.parametrize("T,d,f,E,k", [(37, 64, 192, 4, 2), (300, 320, 192, 2, 2), (1100, 1088, 2112, 16, 2)],
+                         ids=["few_rows", "column_remainders", "more_than_512_large_tiles"])
+def test_weight_gradients_on_both_tile_shapes(L, T, d, f, E, k):
+    spec = _s(T, d, f, E, k)
+    b, _ = run_layer(L, spec, layer_inputs(spec), spec_C(spec))
+    assert expert_tile(b.cfg, "dW1")[0] == (256 if T == 1100 else 128)
+    _check_weight_gradients(b, E)
+
+
+@pytest.mark.parametrize("zipf", [0.0, 1.6], ids=["even", "skewed"])
+def test_weight_gradients_whose_tile_the_row_counts_choose(L, zipf):
+    """Launched on both shapes, of which the row counts let one run: whichever it is
+    writes every element, those of empty experts too."""
+    spec = _s(4096, 512, 2048, 16, 2, zipf_s=zipf)
+    b, _ = run_layer(L, spec, layer_inputs(spec), spec_C(spec))
+    assert expert_tile(b.cfg, "dW1") == expert_tile(b.cfg, "dW2") == (0, 0)
+    fill = host(b.fill)
+    assert (2 * fill.max() * spec.E >= 3 * fill.sum()) == (zipf > 0), fill
+    _check_weight_gradients(b, spec.E)

@@ -17,7 +17,8 @@ def _shape(v):
 
 
 def expert_tile(cfg, product, later=False, cus=256):
-    """(rows, columns) of the tile of one of PRODUCTS; later: a batch partition after the first."""
+    """(rows, columns) of the tile of one of PRODUCTS, (0, 0) where the device picks 128
+    or 256 wide by the row counts; later: a batch partition after the first."""
     return _shape(_expert(ctypes.byref(cfg), PRODUCTS.index(product), later, cus))
 
 
