@@ -338,13 +338,6 @@ static void run_wide_any(const WideCall& w, hipStream_t s) {
   if (t != kTileK256) run_wide_128x128(q, s);
 }
 
-// Expert products.  bf16: blocked operands, wide tiles; outputs that a later
-// product reads (H, A, dH) blocked, the others (expert_out, dXe, which only
-// the gathers read, and the dW products) row-major.  float: the float MFMA
-// kernel, row-major.
-// rows: rows of the output per group (ragged-M: the capacity C, with up to 15
-// alignment rows; ragged-K: M); cols: N.
-//
 // Rows a group is expected to hold, and their standard deviation: the call's
 // assignments spread evenly (T is only a hint here: rows may come from elsewhere).
 static WideCall expert_call(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, bool later) {
@@ -353,30 +346,41 @@ static WideCall expert_call(const moe_cfg& c, WideKind kind, const GemmParams& p
   // A later partition's rows start anywhere in a 16-row block.
   return WideCall{kind, c.act, c.E, rows, cols, expect + (later ? 7.5 : 0.), spread, p};
 }
+// The tile of a float product: the one whose busiest CU has the least work, tiles
+// per CU times area, the 32-tile's extra loads per flop counted as 30 %.
+// Measured, 64-tile against 32-tile: expert_out of 2000 tokens (d 512, f 2048, 8
+// experts) 136 and 125 us, its H 113 and 123; dW of 63 tokens (d 640, f 1280, 8
+// experts) 15 and 23, its H 24 and 15.
+static int f32_tile(const WideCall& w, int cus) {
+  auto cost = [&](int t, double f) {
+    const double n = w.kind >= WK_DW ? std::ceil((double)w.rows / t)
+                                     : 0.5 * (std::ceil(std::max(1., w.expect - w.spread) / t) +
+                                              std::ceil((w.expect + w.spread) / t));
+    return std::ceil(w.groups * n * std::ceil((double)w.cols / t) / cus) * t * t * f;
+  };
+  const bool fits = (double)w.groups * ((w.rows + 46) / 32) * ((w.cols + 31) / 32) <= 1 << 22;   // bounds the grid
+  return fits && cost(32, 1.3) < cost(64, 1.) ? 32 : 64;
+}
+
+// Expert products.  bf16: blocked operands, wide tiles; outputs that a later
+// product reads (H, A, dH) blocked, the others (expert_out, dXe, which only
+// the gathers read, and the dW products) row-major.  float: the float MFMA
+// kernel, row-major.
+// rows: rows of the output per group (ragged-M: the capacity C, with up to 15
+// alignment rows; ragged-K: M); cols: N.
 template <bool B_K, bool RAGGED_K, int EPI>
 static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s,
                        bool later = false) {
   if (rows <= 0 || cols <= 0 || c.E <= 0) return;
   const WideCall w = expert_call(c, kind, p, rows, cols, later);
   if (c.dtype != MOE_BF16) {
-    // The tile whose busiest CU has the least work: tiles per CU times area, the
-    // 32-tile's extra loads per flop counted as 30 %.
-    // Measured, 64-tile against 32-tile: expert_out of 2000 tokens (d 512, f
-    // 2048, 8 experts) 136 and 125 us, its H 113 and 123; dW of 63 tokens (d 640,
-    // f 1280, 8 experts) 15 and 23, its H 24 and 15.
-    auto cost = [&](int t, double f) {
-      const double n = RAGGED_K ? std::ceil((double)rows / t)
-                                : 0.5 * (std::ceil(std::max(1., w.expect - w.spread) / t) +
-                                         std::ceil((w.expect + w.spread) / t));
-      return std::ceil(c.E * n * std::ceil((double)cols / t) / num_cus()) * t * t * f;
-    };
-    const bool fits = (double)c.E * ((rows + 46) / 32) * ((cols + 31) / 32) <= 1 << 22;   // bounds the grid
-    if (fits && cost(32, 1.3) < cost(64, 1.)) launch_f32<1, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
+    if (f32_tile(w, num_cus()) == 32) launch_f32<1, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
     else launch_f32<2, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
     return;
   }
   run_wide_any(w, s);
 }
+
 // Rows per expert block of an [E][C][*] buffer (C rounded up to 16 for bf16).
 static int64_t rows_alloc(const moe_cfg& c) { return c.dtype == MOE_BF16 ? pad16(c.C) : c.C; }
 
@@ -597,8 +601,8 @@ void launch_dense_wide(int64_t M, int N, int K, const void* A, const void* B, bo
   run_wide_any(WideCall{b_nk ? (resid ? WK_NK_RES : WK_NK) : WK_KN, MOE_ACT_IDENTITY, 1, M, N, (double)M, 0., p}, s);
 }
 
-// The tile, (rows << 16) + columns, that the choice above gives a bf16 expert
-// product (kProd*) of a call, or a dense product, on `cus` compute units (0: by the
+// The tile, (rows << 16) + columns, that the choices above give an expert product
+// (kProd*) of a call, or a dense product, on `cus` compute units (0: by the
 // row counts).
 int expert_tile(const moe_cfg& c, int product, bool later, int cus) {
   static const WideKind kinds[kProducts] = {WK_FWD1, WK_NK, WK_DACT, WK_KN, WK_DW, WK_DW};
@@ -609,6 +613,7 @@ int expert_tile(const moe_cfg& c, int product, bool later, int cus) {
   const bool dw = product == kProdDW2 || product == kProdDW1;
   const WideCall w = expert_call(c, kinds[product], p, dw ? (to_f ? c.d_model : c.d_ff) : c.C,
                                  to_f ? c.d_ff : c.d_model, later);
+  if (c.dtype != MOE_BF16) return f32_tile(w, cus) * ((1 << 16) + 1);
   if (dw) {
     const TileK t = tile_k(w, cus);
     return t == kTileKByRows ? 0 : t == kTileK256 ? (256 << 16) + 256 : (128 << 16) + 128;

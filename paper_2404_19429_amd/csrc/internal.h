@@ -98,8 +98,7 @@ void launch_expert_bwd_dx(const moe_cfg& c, const void* dO, const int32_t* rb, c
                           const void* W1, const void* W2, void* dH, void* dXe, void* ws, hipStream_t s);
 void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const void* dO, const void* dH,
                           const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s);
-// The tile, (rows << 16) + columns, of a bf16 expert product (kProd*; later as
-// above) or a dense product on a device of `cus` compute units; 0 where the row
+// The tile, (rows << 16) + columns, of an expert product (kProd*; later as above) or a dense product on a device of `cus` compute units; 0 where the row
 // counts decide on the device.
 int expert_tile(const moe_cfg& c, int product, bool later, int cus);
 int dense_tile(int64_t M, int N, int K, int cus);

@@ -9,13 +9,13 @@ SIZES = [(1531, 768, 3072, 8, 1), (48, 1024, 4096, 16, 2), (2048, 768, 3072, 8, 
          (20000, 512, 2048, 8, 1)]
 
 
-@pytest.mark.parametrize("ksplit", [0, 1])
+@pytest.mark.parametrize("dtype,ksplit", [("bf16", 0), ("bf16", 1), ("f32", 0)])
 @pytest.mark.parametrize("T,d,f,E,k", SIZES)
-def test_half_the_experts_on_half_the_device_take_the_same_tiles(T, d, f, E, k, ksplit):
+def test_half_the_experts_on_half_the_device_take_the_same_tiles(T, d, f, E, k, dtype, ksplit):
     """With the rows per expert and the widths the same, a device with half the
     compute units runs half the tiles in the same rounds."""
-    whole = L.make_cfg(T, d, f, E, k, T, ksplit=ksplit)
-    half = L.make_cfg(T // 2, d, f, E // 2, k, T, ksplit=ksplit)
+    whole = L.make_cfg(T, d, f, E, k, T, dtype=dtype, ksplit=ksplit)
+    half = L.make_cfg(T // 2, d, f, E // 2, k, T, dtype=dtype, ksplit=ksplit)
     for p in PRODUCTS:
         assert expert_tile(whole, p, cus=256) == expert_tile(half, p, cus=128), p
 
