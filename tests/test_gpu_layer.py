@@ -12,6 +12,7 @@ from oracle import moe_oracle as O
 from synth import LayerSpec, layer_inputs, layer_spec
 from tests.gpu_harness import (TOL, assert_close, bf16_ulp, ebuf, host, kept_rows, ksplit_xcds, log, nan_fill,
                                run_layer, spec_C, to_dev)
+from tests.tile_choice import expert_tile
 
 pytestmark = pytest.mark.gpu
 
@@ -196,10 +197,10 @@ def test_batch_partitions_with_capacity_carry_equal_unpartitioned(L):
 
 
 # A shape whose plain-store products (expert_out, dXe: 16 experts x 8 column
-# tiles) leave a short last round on every XCD of the 256-CU device, so with
+# tiles) run on 256 x 256 tiles and leave a short last round on every XCD of the 256-CU device, so with
 # ksplit = 1 their last tiles' K sums are split over several blocks and added
 # by the fix-up kernel.
-KSPLIT_CASE = _s("ksplit", T=4096, d=2048, f=512, E=16, seed=32)
+KSPLIT_CASE = _s("ksplit", T=4096, d=2048, f=1024, E=16, seed=32)
 
 
 def _ksplit_bound(a_rows, b_mat, o1, o2):
@@ -229,6 +230,8 @@ def test_ksplit_products_match_oracle_and_whole_k_sums(L):
     log(f"[ksplit] XCDs whose last round is K-split: {n_split} of 8")
     assert n_split >= 4, "the case no longer exercises the K-split schedule"
     b1 = _check_layer(L, spec)                         # ksplit = 1 (the default)
+    for p in ("fwd2", "dXe"):   # only this tile splits K
+        assert expert_tile(b1.cfg, p, cus=torch.cuda.get_device_properties(0).multi_processor_count) == (256, 256), f"{p} no longer runs the K-split schedule"
     b0, _ = run_layer(L, spec, inp, C, ksplit=0)
     for name in ("logits", "idx", "w", "slot", "fill"):
         np.testing.assert_array_equal(host(getattr(b1, name)), host(getattr(b0, name)), err_msg=name)
@@ -239,6 +242,8 @@ def test_ksplit_products_match_oracle_and_whole_k_sums(L):
     A1, dH1 = ebuf(b1, "A"), ebuf(b1, "dH")
     O1, O0 = ebuf(b1, "O"), ebuf(b0, "O")
     X1, X0 = ebuf(b1, "dXe"), ebuf(b0, "dXe")
+    # the sums in another order do differ somewhere, so the split ran
+    assert (kept_rows(O1, fill) != kept_rows(O0, fill)).any() and (kept_rows(X1, fill) != kept_rows(X0, fill)).any()
     boundO = np.zeros(O1.shape, np.float64)
     worst = 0.0
     for e in range(spec.E):
