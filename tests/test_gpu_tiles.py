@@ -2,11 +2,14 @@
 
 Which shape a product runs on depends on the sizes alone, and every shape sums
 the same 32-wide K steps in order, so with ksplit = 0 a batch cut into
-partitions -- whose products run on smaller tiles than the whole batch's --
-gives the whole batch's bits, forward and dX.  The cases put row counts and
-widths on both sides of the tiles' edges (64, 128, 256 rows; a last column tile
-of 64), down to a few rows per expert.  The weight-gradient products on both of
-their shapes are compared with a float32 product of their own inputs.
+partitions -- whose products may run on smaller tiles than the whole batch's --
+gives the whole batch's bits, forward and dX.  Of each of the four ragged-M
+products the cases of CROSSED compare every shape with another one (each states
+the shapes of the whole batch and of its partitions, checked against the
+library's own choice); row counts and widths end inside tiles.  The other cases
+have few rows per expert, rows just past 16, 64, 128 and 256, and skewed routing.
+The weight-gradient products on their shapes are compared with a float32 product
+of their own inputs.
 """
 from __future__ import annotations
 
@@ -36,21 +39,57 @@ def _s(T, d, f, E, k, **kw):
 
 # (spec, partitions): 16 -> 2 rows per expert; k = E fixes the row counts (every
 # expert gets every token), so 130 / 65 rows stand just past an edge and 258 /
-# 129 / 86 likewise; f = 192 and 320 leave a half-empty last 128-column tile.
+# 129 / 86 likewise.
 CASES = {
     "few_rows": (_s(64, 64, 192, 8, 2), 8),
     "rows_130_65_edges": (_s(130, 192, 320, 4, 4), 2),
     "rows_258_129_86_edges": (_s(258, 128, 832, 2, 2), 3),
     "skewed": (_s(1536, 128, 1024, 16, 2, zipf_s=1.2, cf_num=1, cf_den=1), 4),
     "large_then_small": (_s(4096, 64, 2048, 8, 2, act="relu"), 32),
-    # 8 experts x 270 rows: the whole batch on 192-row tiles, half of it on 128-row ones
     "rows_270_135": (_s(270, 768, 3200, 8, 8), 2),
+}
+# name: (spec, partitions, {products: (tile of the whole batch, of a partition)}), for
+# 256 compute units.  FWD1 and dA share their sizes, and FWD2 and dXe theirs.
+_256, _192, _128, _64W, _64 = (256, 256), (192, 256), (128, 128), (64, 128), (64, 64)
+CROSSED = {
+    "64w_64": (_s(3972, 128, 128, 32, 4), 2, {"fwd1 dA": (_64W, _64), "fwd2 dXe": (_64W, _64)}),
+    "128_64w_64": (_s(6183, 64, 128, 8, 8), 3, {"fwd1 dA": (_128, _64W), "fwd2 dXe": (_128, _64)}),
+    "192_128_64": (_s(4122, 192, 192, 8, 8), 2, {"fwd1 dA": (_192, _64), "fwd2 dXe": (_192, _128)}),
+    "256_64w": (_s(6048, 64, 320, 16, 4, act="gelu_erf"), 3, {"fwd1 dA": (_256, _64W), "fwd2 dXe": (_64, _64)}),
+    "256_64": (_s(6108, 320, 128, 8, 4), 4, {"fwd1 dA": (_64W, _64), "fwd2 dXe": (_256, _64)}),
 }
 
 
+def test_crossed_cases_compare_every_shape_of_every_product(L):
+    """(the shapes each comparison joins are one component, so all of them are equal)"""
+    for products in ("fwd1 dA", "fwd2 dXe"):
+        joined = {_64}
+        for _ in CROSSED:
+            for _, _, tiles in CROSSED.values():
+                if joined & set(tiles[products]):
+                    joined |= set(tiles[products])
+        assert joined == {_256, _192, _128, _64W, _64}, (products, joined)
+
+
+@pytest.mark.parametrize("case", list(CROSSED))
+def test_partitions_on_other_tiles_are_bitwise_the_whole_batch(L, case):
+    spec, n, tiles = CROSSED[case]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for T, which in ((spec.T, 0), (spec.T // n, 1)):
+        cfg = L.make_cfg(T, spec.d, spec.f, spec.E, spec.k, spec_C(spec), 1, spec.dtype, spec.act, spec.renorm, ksplit=0)
+        for products, shapes in tiles.items():
+            for p in products.split():
+                assert expert_tile(cfg, p, cus=cus) == shapes[which], (p, T)
+    _partitions_equal_whole(L, case, spec, n)
+
+
 @pytest.mark.parametrize("case", list(CASES))
-def test_partitions_on_smaller_tiles_are_bitwise_the_whole_batch(L, case):
+def test_partitions_are_bitwise_the_whole_batch(L, case):
     spec, n = CASES[case]
+    _partitions_equal_whole(L, case, spec, n)
+
+
+def _partitions_equal_whole(L, case, spec, n):
     inp = layer_inputs(spec)
     C = spec_C(spec)
     log(f"[tiles] {case}: T={spec.T} in {n} partitions, C={C}")
