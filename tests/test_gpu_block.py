@@ -169,6 +169,19 @@ def test_partitions_equal_unpartitioned(L, case):
         assert (host(b1["slot"]) < 0).any(), "the drop case should drop tokens"
 
 
+def test_partitions_whose_attention_takes_the_shorter_query_tile(L):
+    """The whole batch has two 128-query blocks per compute unit, a quarter of it fewer,
+    so its attention runs the 64-query form: the bits stay the same."""
+    spec = block_spec(B=64, S=130, d=512, heads=4, moe_f=128, moe_E=8, n_chunks=4, seed=25)
+    blocks = lambda n: -(-spec.S // 128) * spec.B // n * spec.heads
+    assert blocks(4) < 2 * torch.cuda.get_device_properties(0).multi_processor_count <= blocks(1)
+    dev = _upload(L, block_inputs(spec))
+    _, _, b1 = run_block(L, spec, dev, 1)
+    for n in (4, 64):
+        _, _, bn = run_block(L, spec, dev, n)
+        _assert_partition_equivalent(b1, bn, spec.moe.E, f"{n} partitions vs 1")
+
+
 def test_deferred_weight_stream_and_repeat_are_bitwise_stable(L):
     spec = SMALL["B2_S200_d256_f256_E8_2chunks"]
     dev = _upload(L, block_inputs(spec))
