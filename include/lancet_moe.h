@@ -188,8 +188,9 @@ moe_status moe_dispatch_noalloc(const moe_cfg* cfg, const void* x, const int32_t
  *   The whole batch decides the order, so there is no carry-in: partitions of
  *   the batch may only start after this call (the paper's pipelining after the
  *   gate).  ws: moe_workspace_bytes(cfg, MOE_CALL_DISPATCH_BPR) bytes of device
- *   memory.  The sort: 4096-token tiles sorted in LDS, then merged by binary
- *   search (deterministic, no atomics on device memory). */
+ *   memory.  The sort: tiles of 1024, 2048 or 4096 tokens sorted in LDS and, if
+ *   there are several, merged by binary search (deterministic, no atomics on
+ *   device memory). */
 moe_status moe_dispatch_bpr(const moe_cfg* cfg, const void* x, const float* logits, const int32_t* idx,
                             int32_t* fill, int32_t* slot, void* send_buf, int32_t* order, void* ws, size_t ws_bytes,
                             moe_stream_t stream);

@@ -232,13 +232,15 @@ static void launch_f32(const GemmParams& p, int groups, int64_t rows, int cols, 
 size_t expert_sk_ws_bytes(const moe_cfg& c) { return c.dtype == MOE_BF16 ? (size_t)kSkPartElems * sizeof(float) : 0; }
 
 // Tile choice of the wide kernel's ragged-M products.  A product's blocks
-// advance in rounds of `slots` tiles.  A tile takes K / 32 steps of `full` ns
-// when the round fills the chip, `part` ns when at most one block is on a CU,
+// advance in rounds of per_cu tiles per CU.  A tile takes K / 32 steps of `full`
+// ns when the round fills the chip, `part` ns when at most one block is on a CU,
 // and `store` ns for its epilogue (two outputs, or an output and H).  The
 // larger tile moves fewer bytes per flop (its step is the cheapest per output
 // element); the smaller one wastes less on ragged rows and on rounds that leave
 // CUs idle.  The constants are measured (whole products on one MI355X divided
-// by their steps); the shape with the least modelled time runs.  Where the line
+// by their steps); the shape with the least modelled time runs.  The rows are
+// taken as spread evenly over the groups: how a routing is skewed shows on the
+// device only.  Where the line
 // lies, 256-tiles against the choice: expert_out of 1531 tokens (d 768, f 3072,
 // 8 experts) 68 -> 26 us, of 48 tokens (d 1024, f 4096, 16 experts) 75 -> 44,
 // of 2048 tokens (d 768) 73 -> 40, of 3108 tokens 78 -> 65; at 4096 tokens

@@ -82,7 +82,8 @@ __device__ __forceinline__ int mn_lds_off(int k, int col) {
 constexpr int kPanelN = 8;
 
 // ------------------------------------------------------ wide bf16 MFMA tiles
-// The expert products at full size.  256 x 256 block tiles, one block per CU,
+// The largest shape (tile shapes: below), which the expert products take at full
+// size.  256 x 256 block tiles, one block per CU,
 // eight waves in a 2 x 4 grid, each owning a 128 x 64 tile (32 accumulator
 // fragments) -- two waves per SIMD, so one wave's MFMAs issue while the other
 // waits on memory.  Against 128 x 128 block tiles this halves the operand
@@ -210,14 +211,14 @@ __device__ __forceinline__ void acc_pin_mem(f32x4 (&a)[N]) {
   for (int i = 0; i < N; i += 2) asm volatile("" : "+a"(a[i]), "+a"(a[i + 1])::"memory");
 }
 
-// One operand's loads for the K-steps of a tile (256 rows or columns x 32 K
+// One operand's loads for the K-steps of a tile (ROWS rows or columns x 32 K
 // per stage, blocked source), as raw buffer loads into LDS.  The buffer
 // descriptor spans the operand's group (expert) from the current K-step on, so
 // a K-step only moves the descriptor (scalar adds), and a lane whose chunk is
 // out of range carries bit 31 in its offset, which the buffer range check
 // turns into zeros.  K-contiguous (KC): the chunk of fragment q is a whole
-// 16 x 32 block, rows past `lim` read zeros.  MN-contiguous: 32 K rows x 256
-// columns as 2 x 8 blocks, each lane's chunk placed at its swizzled position;
+// 16 x 32 block, rows past `lim` read zeros.  MN-contiguous: 32 K rows x ROWS
+// columns as 2 x ROWS / 32 blocks, each lane's chunk placed at its swizzled position;
 // columns past `lim` and, with KCHK, K rows outside [klo, khi) read zeros.
 constexpr int kBufCfg = 0x00020000;   // buffer descriptor word 3: raw 32-bit data, gfx9 family
 constexpr uint32_t kOob = 0x80000000u;
@@ -330,8 +331,8 @@ __device__ __forceinline__ WSched wide_sched(int n, int nslot, bool allow_split)
 // Lane-per-group tile counts of a wide product and their prefixes (groups <= 64).
 // Ragged-K, or ragged-M without SEP: every tile of a group (with rows); ragged-K
 // prefixes run over the groups by rows, most first.
-// Ragged-M with SEP: the full M-tiles (256 rows) and, separately, the short
-// last M-tile of a group whose rows are not a multiple of 256; tile numbers
+// Ragged-M with SEP: the full M-tiles (BM rows) and, separately, the short
+// last M-tile of a group whose rows are not a multiple of BM; tile numbers
 // [0, NF) are the full tiles, [NF, NF + NP) the short ones, so a schedule can
 // place the short (cheaper) tiles last.
 struct WPrefix {
@@ -914,7 +915,7 @@ gemm_wide_kernel(GemmParams p, int tilesM, int tilesN, int groups) {
     };
     if constexpr (PRE == 0) sync();
     // The reads are unconditional (branch-free, so pending registers are never
-    // copied); after the last step they read a stage no load is writing.
+    // copied); what they read after the last step is not used.
     const uint32_t ra0 = base_a(st, 0), ra1 = AK ? ra0 : base_a(st, 1);
     const uint32_t rb0 = base_b(st, 0), rb1 = BKK ? rb0 : base_b(st, 1);
     __builtin_amdgcn_sched_barrier(0);
