@@ -240,9 +240,9 @@ size_t expert_sk_ws_bytes(const moe_cfg& c) { return c.dtype == MOE_BF16 ? (size
 // CUs idle.  The constants are measured (whole products on one MI355X divided
 // by their steps); the shape with the least modelled time runs.  The rows are
 // taken as spread evenly over the groups: how a routing is skewed shows on the
-// device only.  Where the line
-// lies, 256-tiles against the choice: expert_out of 1531 tokens (d 768, f 3072,
-// 8 experts) 68 -> 26 us, of 48 tokens (d 1024, f 4096, 16 experts) 75 -> 44,
+// device only.
+// Where the line lies, 256-tiles against the choice: expert_out of 1531 tokens (d
+// 768, f 3072, 8 experts) 68 -> 26 us, of 48 tokens (d 1024, f 4096, 16 experts) 75 -> 44,
 // of 2048 tokens (d 768) 73 -> 40, of 3108 tokens 78 -> 65; at 4096 tokens
 // (d 1024, 16 experts) 128-tiles lose (128 against 110), and the fused products
 // keep 256-tiles from 2048 tokens on (37 against 41).  192-row tiles, for rows
