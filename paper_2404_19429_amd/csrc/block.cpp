@@ -69,14 +69,17 @@ hipError_t order(hipStream_t a, hipStream_t b) {
   return hipStreamWaitEvent(b, ev, 0);
 }
 
-// b waits for the caller's earlier work on a.  In a capture of b, a stream that
-// is not part of it has none that the graph could wait for.
-hipError_t order_earlier(hipStream_t a, hipStream_t b) {
+// Whether b can wait for earlier work on a.  In a capture of b, a stream that is
+// not part of it has none that the graph could wait for; a captured a cannot be
+// ordered with a b that is not.
+hipError_t has_earlier_work(hipStream_t a, hipStream_t b, bool* out) {
   hipStreamCaptureStatus ca = hipStreamCaptureStatusNone, cb = hipStreamCaptureStatusNone;
+  *out = false;
   if (a == b) return hipSuccess;
+  HIP_TRY(hipStreamIsCapturing(a, &ca));
   HIP_TRY(hipStreamIsCapturing(b, &cb));
-  if (cb != hipStreamCaptureStatusNone) HIP_TRY(hipStreamIsCapturing(a, &ca));
-  return ca == cb ? order(a, b) : hipSuccess;
+  *out = ca == cb;
+  return ca == cb || cb != hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureIsolation;
 }
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -200,6 +203,8 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
     // us).  It still comes after the caller's earlier work on the data-movement
     // stream and before its later work there (3 and 16 us of that forward).
     const hipStream_t Sd = n == 1 ? Sc : Sx;
+    bool wait_sx = false;
+    if (n == 1) HIP_TRY(has_earlier_work(Sx, Sc, &wait_sx));
     HIP_TRY(order(Sc, Sd));  // the data-movement stream starts after the caller's earlier work
     if (!mc.wpacked) launch_pack_weights(mc, W.W1, W.W2, A.W1p, A.W2p, Sc);  // expert weights as the GEMMs read them
     launch_pack_rows(W.Wqkv, Wqkv_b, d3, d, Sc);
@@ -218,7 +223,8 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       launch_ln_fwd(bf(A.h, t0 * d), W.ln2_g, W.ln2_b, bfm(A.m, t0 * d), A.ln2_mean + t0, A.ln2_rstd + t0, Tc, d, Sc);
       launch_gate(pc, bf(A.m, t0 * d), W.Wg, nullptr, A.logits + t0 * E, A.idx + t0 * k, A.w + t0 * k, Sc);
       HIP_TRY(hipGetLastError());
-      HIP_TRY(n == 1 ? order_earlier(Sx, Sc) : order(Sc, Sx));
+      if (n > 1) HIP_TRY(order(Sc, Sx));
+      else if (wait_sx) HIP_TRY(order(Sx, Sc));
       launch_dispatch(pc, bf(A.m, t0 * d), A.idx + t0 * k, i == 0 ? nullptr : A.fill + (int64_t)(i - 1) * E,
                       A.fill + (int64_t)i * E, A.slot + t0 * k, A.send_buf, wsb + L.disp, Sd);
       HIP_TRY(hipGetLastError());

@@ -126,10 +126,8 @@ def test_graph_replay_full_size_equals_eager(L):
             assert torch.equal(getattr(b, n), getattr(ref_b, n)), f"{n} differs on replay {rep}"
 
 
-@pytest.mark.parametrize("n", [1, 2])
-def test_block_captured_on_three_streams_replays_equal_eager(L, n):
-    """A block step whose two side streams are not part of the capture before the
-    call: it brings them in, joins them, and every replay gives the eager bits."""
+def _block(L, n):
+    """A small block: (cfg, weights, x, dy, buffers())."""
     from synth import block_inputs, block_spec
     from oracle import moe_oracle as O
     spec = block_spec(B=2, S=100, d=256, heads=2, moe_f=256, moe_E=8, n_chunks=n, seed=24)
@@ -139,12 +137,21 @@ def test_block_captured_on_three_streams_replays_equal_eager(L, n):
     inp = block_inputs(spec)
     w = {q: to_dev(inp[q], torch.bfloat16).reshape(-1) for q in L.BLOCK_WEIGHTS}
     x, dy = (to_dev(inp[q], torch.bfloat16).reshape(-1) for q in ("x", "dy"))
-    side = [torch.cuda.Stream() for _ in range(2)]
 
     def buffers():
         b = L.alloc_block(cfg, n)
         b["out"], b["dx"] = torch.empty_like(x), torch.empty_like(x)
         return b
+
+    return cfg, w, x, dy, buffers
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_block_captured_on_three_streams_replays_equal_eager(L, n):
+    """A block step whose two side streams are not part of the capture before the
+    call: it brings them in, joins them, and every replay gives the eager bits."""
+    cfg, w, x, dy, buffers = _block(L, n)
+    side = [torch.cuda.Stream() for _ in range(2)]
 
     def step(b):
         L.moe_block_chunked(cfg, w, b, x, b["out"], dy, b["dx"], b, 3, n, [torch.cuda.current_stream()] + side, b["ws"])
@@ -164,3 +171,21 @@ def test_block_captured_on_three_streams_replays_equal_eager(L, n):
         torch.cuda.synchronize()
         for q in names:
             assert torch.equal(b[q], ref[q]), f"{q} differs on replay {rep}"
+
+
+def test_block_refuses_a_captured_data_movement_stream_alone(L):
+    """streams[1] in a capture that streams[0] is not part of: the two cannot be
+    ordered, and the call is refused before it launches anything."""
+    cfg, w, x, dy, buffers = _block(L, 1)
+    b = buffers()
+    b["out"].fill_(7)
+    s = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s[1], capture_error_mode="relaxed"):
+        with pytest.raises(L.MoeError) as e:
+            L.moe_block_chunked(cfg, w, None, x, b["out"], None, None, b, L.MOE_BLOCK_FWD, 1, [s[0], s[1], s[0]], b["ws"])
+        b["dx"].zero_()
+    torch.cuda.synchronize()
+    assert e.value.status == L.MOE_ELAUNCH
+    assert bool((b["out"] == 7).all())
