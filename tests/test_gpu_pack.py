@@ -1,6 +1,6 @@
 """moe_pack_weights at its edges: the float copy of a few elements and of a last
-part-filled block, the bf16 blocks of matrices whose widths have 64, 128 and 256
-columns as their largest common launch block."""
+part-filled block, the bf16 blocks of matrices that take 64, 128 and 256 columns per
+launch block, whole and ending inside one."""
 from __future__ import annotations
 
 import pytest
@@ -24,7 +24,7 @@ def _packed(W, dtype):
 
 
 SHAPES = [("f32", 1, 8, 8), ("f32", 5, 72, 104), ("f32", 3, 512, 1024), ("bf16", 1, 64, 64), ("bf16", 3, 192, 320),
-          ("bf16", 2, 1024, 128), ("bf16", 3, 256, 768)]
+          ("bf16", 2, 1024, 128), ("bf16", 3, 256, 768), ("bf16", 1, 4032, 4160), ("bf16", 1, 8128, 256)]
 
 
 def _weights(L, dtype, E, d, f):
