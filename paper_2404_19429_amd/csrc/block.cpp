@@ -314,15 +314,15 @@ hipError_t run_block(const moe_block_cfg& c, const moe_block_weights& W, const m
       HIP_TRY(mark(op, 0, Sw));
       switch (op) {
         case MOE_BOP_DW_EXPERT:
-          launch_expert_bwd_dw(mc, A.send_buf, A.A, A.dO, A.dH, nullptr, fill_end, G->dW1, G->dW2, Sw);
+          launch_expert_bwd_dw(mc, A.send_buf, A.A, A.dO, A.dH, nullptr, fill_end, G->dW1, G->dW2, Sw, Sw != Sc);
           break;
         case MOE_BOP_DWG: launch_dwg(mc, A.m, A.dlogits, G->dWg, wsb + L.dw, Sw); break;
         case MOE_BOP_DLN2:
           launch_ln_gain_reduce((float*)(wsb + L.ln2), T, d, G->dln2_g, G->dln2_b, Sw);
           break;
-        case MOE_BOP_DWO: launch_dense_wgrad(d, d, T, A.dh, A.attn, G->dWo, wsb + L.wgp, Sw); break;  // dh^T o
+        case MOE_BOP_DWO: launch_dense_wgrad(d, d, T, A.dh, A.attn, G->dWo, wsb + L.wgp, Sw, Sw != Sc); break;  // dh^T o
         case MOE_BOP_DWQKV:
-          launch_dense_wgrad((int)d3, d, T, A.dqkv, A.a, G->dWqkv, wsb + L.wgp, Sw);  // dWqkv = dqkv^T a
+          launch_dense_wgrad((int)d3, d, T, A.dqkv, A.a, G->dWqkv, wsb + L.wgp, Sw, Sw != Sc);  // dWqkv = dqkv^T a
           break;
         default:
           launch_ln_gain_reduce((float*)(wsb + L.ln1), T, d, G->dln1_g, G->dln1_b, Sw);

@@ -305,11 +305,21 @@ static int tile_m(const WideCall& w, int cus) {
 // of 192 large tiles.  dW of 256 large tiles and 8192 rows each, 128- against
 // 256-tiles (two launches) 645 and 505 us, of 416 tiles and 1260 rows 191 and 170; of
 // 512 tiles and 75 rows 45 and 50.
+//
+// Where other work runs beside the product (the block's weight stream), it fills the
+// CUs that a part-filled round leaves idle, and the tile with the least CU time wins:
+// 256-tiles from three quarters of a round on.  Block backward on three streams, the choice above
+// against 256-tiles: 6 x 2501 tokens (d 1536, f 3072, 4 experts; 288 large tiles, dWo
+// 144, dWqkv 432) 2561 and 2296 us, 8 x 2048 (d 1024, f 4096, 8 experts; 512, 64, 192)
+// 1877 and 1762; with all products below a full round 128-tiles stay ahead (4 x 500
+// tokens, d 512, f 2048, 8 experts; 128, 16, 48) 208 and 244.  (Nor is an idle launch
+// little there: its blocks wait for CUs that the other work holds.)
 enum TileK { kTileK128, kTileK256, kTileKByRows };
 static TileK tile_k(const WideCall& w, int cus) {
   const auto tiles = [&](int t) { return (w.rows + t - 1) / t * ((w.cols + t - 1) / t) * w.groups; };
   const int64_t large = tiles(256);
   if (large > 2 * cus) return kTileK256;
+  if (w.beside && 4 * large >= 3 * cus) return kTileK256;
   if (w.kind == WK_WGF32) {
     const int64_t three = cus * 3 / 4;
     return w.expect >= 512. && 3 * ((large + three - 1) / three) >= 4 * ((large + cus - 1) / cus) ? kTileK256
@@ -372,9 +382,10 @@ static int f32_tile(const WideCall& w, int cus) {
 // alignment rows; ragged-K: M); cols: N.
 template <bool B_K, bool RAGGED_K, int EPI>
 static void run_expert(const moe_cfg& c, WideKind kind, const GemmParams& p, int64_t rows, int cols, hipStream_t s,
-                       bool later = false) {
+                       bool later = false, bool beside = false) {
   if (rows <= 0 || cols <= 0 || c.E <= 0) return;
-  const WideCall w = expert_call(c, kind, p, rows, cols, later);
+  WideCall w = expert_call(c, kind, p, rows, cols, later);
+  w.beside = beside;
   if (c.dtype != MOE_BF16) {
     if (f32_tile(w, num_cus()) == 32) launch_f32<1, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
     else launch_f32<2, B_K, RAGGED_K, EPI>(p, c.E, rows, cols, s);
@@ -510,7 +521,7 @@ void launch_expert_bwd_dx(const moe_cfg& c, const void* dO, const int32_t* rb, c
 }
 
 void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const void* dO, const void* dH,
-                          const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s) {
+                          const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s, bool beside) {
   const int64_t d = c.d_model, f = c.d_ff, C = c.C, Cp = rows_alloc(c);
   // dW2_e [d][f] = dO_e^T A_e : A-operand(m, k) = dO[e][k][m], B(k, n) = A[e][k][n]
   // (wpacked: written in the blocked layout of the packed weights)
@@ -519,10 +530,10 @@ void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const 
   GemmParams p1{dH, f, Cp * f, X, d, Cp * d, dW1, d, f * d, nullptr, nullptr, rb, re, (int)f, (int)d, 0, c.act, (int)C};
   const bool blk = c.wpacked && c.dtype == MOE_BF16;
   bool tb = ptimer_begin(kProdDW2, s);
-  run_expert<false, true, EPI_STORE>(c, blk ? WK_DW_BLK : WK_DW, p2, d, (int)f, s);
+  run_expert<false, true, EPI_STORE>(c, blk ? WK_DW_BLK : WK_DW, p2, d, (int)f, s, false, beside);
   ptimer_end(tb, s);
   tb = ptimer_begin(kProdDW1, s);
-  run_expert<false, true, EPI_STORE>(c, blk ? WK_DW_BLK : WK_DW, p1, f, (int)d, s);
+  run_expert<false, true, EPI_STORE>(c, blk ? WK_DW_BLK : WK_DW, p1, f, (int)d, s, false, beside);
   ptimer_end(tb, s);
 }
 
@@ -553,13 +564,15 @@ size_t wgrad_ws_bytes(int M, int N) { return (size_t)kWgradSplit * M * N * sizeo
 // product with K split into wgrad_ksplit(M, N) token ranges of equal length
 // (multiples of 32), one float partial per range in `part`
 // (wgrad_ws_bytes(M, N) bytes), then their sum in range order.
-void launch_dense_wgrad(int M, int N, int64_t K, const void* A, const void* B, void* C, void* part, hipStream_t s) {
+void launch_dense_wgrad(int M, int N, int64_t K, const void* A, const void* B, void* C, void* part, hipStream_t s,
+                        bool beside) {
   if (M <= 0 || N <= 0) return;
   const int S = kWgradSplit;
   const int64_t MN = (int64_t)M * N;
   GemmParams p{A, M, 0, B, N, 0, part, N, MN, nullptr, nullptr, nullptr, nullptr, M, N, 0, 0, (int)K};
   p.kchunk = (int)(((K + S - 1) / S + 31) / 32 * 32);
-  run_wide_any(WideCall{WK_WGF32, MOE_ACT_IDENTITY, S, M, N, (double)std::min<int64_t>(K, p.kchunk), 0., p}, s);
+  run_wide_any(WideCall{WK_WGF32, MOE_ACT_IDENTITY, S, M, N, (double)std::min<int64_t>(K, p.kchunk), 0., p, beside},
+               s);
   hipLaunchKernelGGL(gemm_wgrad_reduce_kernel, dim3((unsigned)((MN / 8 + 255) / 256)), dim3(256), 0, s,
                      (const float*)part, S, MN, (uint16_t*)C);
 }

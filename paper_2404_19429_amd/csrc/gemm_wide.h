@@ -1106,6 +1106,7 @@ struct WideCall {
   double expect;  // rows a group is expected to hold (WK_WGF32: its K), and their
   double spread;  // standard deviation (hints for the tile choice)
   GemmParams p;
+  bool beside = false;   // ragged-K: other work runs beside it on another stream
 };
 
 constexpr int64_t kSkPartElems = (int64_t)256 * 256 * 256;   // floats of the K-split's partial tiles (one per block)

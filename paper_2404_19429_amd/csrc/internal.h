@@ -90,14 +90,16 @@ void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void*
 // gemm.hip: expert GEMMs over [E][C][*] buffers with per-expert row ranges.
 // The row-ragged products take a workspace of expert_sk_ws_bytes(c) bytes
 // (partial tiles and counters of their K-split schedule; unused for float).
-// later: a batch partition after the first (a hint for the tile choice).
+// later: a batch partition after the first; beside: other work runs at the same time
+// on another stream (hints for the tile choice).
 size_t expert_sk_ws_bytes(const moe_cfg& c);
 void launch_expert_fwd(const moe_cfg& c, const void* X, const int32_t* rb, const int32_t* re, const void* W1,
                        const void* W2, void* H, void* A, void* O, void* ws, hipStream_t s, bool later = false);
 void launch_expert_bwd_dx(const moe_cfg& c, const void* dO, const int32_t* rb, const int32_t* re, const void* H,
                           const void* W1, const void* W2, void* dH, void* dXe, void* ws, hipStream_t s);
 void launch_expert_bwd_dw(const moe_cfg& c, const void* X, const void* A, const void* dO, const void* dH,
-                          const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s);
+                          const int32_t* rb, const int32_t* re, void* dW1, void* dW2, hipStream_t s,
+                          bool beside = false);
 // The tile, (rows << 16) + columns, of an expert product (kProd*; later as above) or a dense product on a device of `cus` compute units; 0 where the row
 // counts decide on the device.
 int expert_tile(const moe_cfg& c, int product, bool later, int cus);
@@ -116,7 +118,8 @@ hipError_t product_times(double* ms, int32_t* counts);
 // (sum over K rows), on the wide kernel with K split into token ranges whose
 // float partials go to `part` (wgrad_ws_bytes(M, N) bytes).
 size_t wgrad_ws_bytes(int M, int N);
-void launch_dense_wgrad(int M, int N, int64_t K, const void* A, const void* B, void* C, void* part, hipStream_t s);
+void launch_dense_wgrad(int M, int N, int64_t K, const void* A, const void* B, void* C, void* part, hipStream_t s,
+                        bool beside = false);
 // Row-major [M][K] -> blocked [pad16(M)][K] (K a multiple of 32), and dense
 // products on the wide kernel over blocked operands (see gemm.hip).
 void launch_pack_rows(const void* src, void* dst, int64_t M, int K, hipStream_t s);

@@ -192,6 +192,16 @@ def test_deferred_weight_stream_and_repeat_are_bitwise_stable(L):
     _assert_bitwise(b1, b3, spec.moe.E, "repeat")
 
 
+def test_weight_gradients_beside_the_chain_are_bitwise_those_alone(L):
+    """On a stream of their own the weight gradients of 192 large tiles and more (here
+    dW1, dW2 and dWqkv) take the larger tile, on the chain's stream the smaller one."""
+    spec = block_spec(B=2, S=130, d=1024, heads=8, moe_f=1536, moe_E=8, n_chunks=1, seed=26)
+    dev = _upload(L, block_inputs(spec))
+    _, _, b1 = run_block(L, spec, dev, 1)
+    _, _, b2 = run_block(L, spec, dev, 1, same_stream=True)
+    _assert_bitwise(b1, b2, spec.moe.E, "three streams vs one")
+
+
 def test_forward_then_backward_passes_equal_combined(L):
     spec = SMALL["B4_S37_d128_f128_E4_4chunks"]
     dev = _upload(L, block_inputs(spec))
