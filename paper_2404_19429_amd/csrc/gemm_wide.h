@@ -365,13 +365,15 @@ __device__ __forceinline__ WPrefix wide_tile_prefix(const GemmParams& p, int lan
   P.span = span;
   if constexpr (RAGGED_K) {
     // Groups by rows, most first (ties by index): a tile is as long as its group,
-    // and a round of the schedule then holds tiles of nearly one length.
-    int before = 0, all = 0;
-    for (int h = 0; h < groups; ++h) {
-      const int ch = __builtin_amdgcn_readlane(cnt, h), sh = __builtin_amdgcn_readlane(span, h);
-      all += ch;
-      if (sh > span || (sh == span && h < lane)) before += ch;
-    }
+    // and a round of the schedule then holds tiles of nearly one length.  One key per
+    // group (rows past 2^25 count as that many), so a group costs a broadcast, a
+    // comparison and an addition.
+    const int key = min(span, (1 << 25) - 1) * 64 + 63 - lane;
+    int ahead = 0;
+    for (int h = 0; h < groups; ++h) ahead += __builtin_amdgcn_readlane(key, h) > key ? 1 : 0;
+    const int per = tilesM * tilesN;   // (of a group with rows; the groups without are the last)
+    const int before = per * ahead;
+    const int all = per * __popcll(__ballot(span > 0));
     P.excl = before;
     P.incl = before + cnt;
     P.inclP = P.exclP = 0;
