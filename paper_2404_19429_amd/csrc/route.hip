@@ -1268,34 +1268,30 @@ namespace lmoe {
 
 // ------------------------------------------------------------- weight packing
 // Row-major [R][X] matrices -> blocked layout (bf16; R a multiple of 16, X of
-// 32), W1 and W2 in one launch.  A block takes 16 rows x CW columns: it loads whole
-// row pieces of 2 CW bytes and through LDS stores each 16 x 32 block as one
-// contiguous KiB.  HBM bound: reads and writes each weight once.  CW is the largest
-// of 256, 128 and 64 whose last columns leave at most a 64th of the lanes idle in
-// either width: two matrices of 256 MiB (d 2048, f 8192, 8 experts) with 256, 128 and
-// 64 columns 173, 192 and 206 us (a thread per 16 bytes storing 64-byte pieces, a
-// launch per matrix, 185); of 265 MiB (d 448, f 6464) 198, 194 and 184 (189); of 36
-// MiB (d 768, f 3072) 22.3, 22.2 and 22.1 (23.6).  512 columns per block, and 64 rows
-// with four loads in flight per lane, were slower than the best of these.
-template <int CW>
-__global__ __launch_bounds__(2 * CW) void pack_blocked_kernel(const uint16_t* __restrict__ W1, uint16_t* __restrict__ P1,
-                                                              int X1, int64_t n1, const uint16_t* __restrict__ W2,
-                                                              uint16_t* __restrict__ P2, int X2) {
-  __shared__ __attribute__((aligned(16))) uint16_t tile[16 * CW];
+// 32), W1 and W2 in one launch.  A block takes the next eight 16 x 32 blocks of the
+// copy (n of them per matrix), which lie side by side in a strip of 16 rows (or end
+// one and begin the next): it loads row pieces of 512 bytes and through LDS stores 8
+// contiguous KiB.  HBM bound: reads and writes each weight once.  Two matrices of
+// 512 MiB (d 2048, f 8192, 16 experts) 356 us, of 36 MiB (d 768, f 3072) 22.2, of
+// 265 MiB (d 448, f 6464) 188; a thread per 16 bytes storing 64-byte pieces, a launch
+// per matrix, 377, 23.8 and 186; 128 columns of one strip per block 386, 22.2 and 195.
+__global__ __launch_bounds__(512) void pack_blocked_kernel(const uint16_t* __restrict__ W1, uint16_t* __restrict__ P1,
+                                                           uint32_t X1, int64_t n1, const uint16_t* __restrict__ W2,
+                                                           uint16_t* __restrict__ P2, uint32_t X2, uint32_t n) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[8 * 512];
   const bool one = blockIdx.x < n1;
-  const int64_t b = one ? blockIdx.x : blockIdx.x - n1;
+  const uint32_t t0 = (uint32_t)(one ? blockIdx.x : blockIdx.x - n1) * 8;
   const uint16_t* src = one ? W1 : W2;
   uint16_t* dst = one ? P1 : P2;
-  const int X = one ? X1 : X2, cg = (X + CW - 1) / CW;
-  const int64_t rb = b / cg;                        // 16-row block over all matrices
-  const int c0 = (int)(b - rb * cg) * CW;
-  const int r = threadIdx.x / (CW / 8), c = threadIdx.x % (CW / 8) * 8;
+  const uint32_t X = one ? X1 : X2, kb = X / 32;
+  const uint32_t j = threadIdx.x % 32 / 4, r = threadIdx.x / 32, c = threadIdx.x % 4 * 8;
+  const uint32_t t = t0 + j, rb = t / kb;
   u32x4 v = u32x4{0u, 0u, 0u, 0u};
-  if (c0 + c < X) v = *reinterpret_cast<const u32x4*>(src + (rb * 16 + r) * X + c0 + c);
-  *reinterpret_cast<u32x4*>(tile + (c >> 5) * 512 + r * 32 + (c & 31)) = v;
+  if (t < n) v = *reinterpret_cast<const u32x4*>(src + ((int64_t)rb * 16 + r) * X + (t - rb * kb) * 32 + c);
+  *reinterpret_cast<u32x4*>(tile + j * 512 + r * 32 + c) = v;
   __syncthreads();
-  if (c0 + (threadIdx.x >> 6) * 32 < X)
-    *reinterpret_cast<u32x4*>(dst + rb * 16 * X + (int64_t)c0 * 16 + threadIdx.x * 8) =
+  if (t0 + (threadIdx.x >> 6) < n)
+    *reinterpret_cast<u32x4*>(dst + (int64_t)t0 * 512 + threadIdx.x * 8) =
         *reinterpret_cast<const u32x4*>(tile + threadIdx.x * 8);
 }
 
@@ -1319,20 +1315,16 @@ void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void*
   const size_t bytes = (size_t)(E * f * d) * (c.dtype == MOE_BF16 ? 2 : 4);
   const bool over = (uintptr_t)W2p < (uintptr_t)W1 + bytes && (uintptr_t)W1 < (uintptr_t)W2p + bytes;
   if (c.dtype == MOE_BF16) {
-    auto groups = [](int64_t X, int cw) { return (X + cw - 1) / cw; };
-    auto fits = [&](int64_t X, int cw) { return 64 * (groups(X, cw) * cw - X) <= X; };
-    const int cw = fits(d, 256) && fits(f, 256) ? 256 : fits(d, 128) && fits(f, 128) ? 128 : 64;
-    const int64_t n1 = E * (f / 16) * groups(d, cw), n2 = E * (d / 16) * groups(f, cw);
-    auto kern = cw == 256 ? pack_blocked_kernel<256> : cw == 128 ? pack_blocked_kernel<128> : pack_blocked_kernel<64>;
+    const int64_t n = E * f * d / 512, nb = (n + 7) / 8;   // (far below 2^32: four such matrices fit the card)
     auto go = [&](int64_t b1, int64_t b2) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)(b1 + b2)), dim3(2 * cw), 0, s, (const uint16_t*)W1, (uint16_t*)W1p, (int)d,
-                         b1, (const uint16_t*)W2, (uint16_t*)W2p, (int)f);
+      hipLaunchKernelGGL(pack_blocked_kernel, dim3((unsigned)(b1 + b2)), dim3(512), 0, s, (const uint16_t*)W1,
+                         (uint16_t*)W1p, (uint32_t)d, b1, (const uint16_t*)W2, (uint16_t*)W2p, (uint32_t)f, (uint32_t)n);
     };
-    if (n1 + n2 <= 1 << 22 && !over) {
-      go(n1, n2);
+    if (2 * nb <= 1 << 22 && !over) {
+      go(nb, nb);
     } else {   // (the launch's thread count is 32 bits)
-      go(n1, 0);
-      go(0, n2);
+      go(nb, 0);
+      go(0, nb);
     }
   } else {
     const int64_t n = E * f * d / 4, most = (int64_t)1 << 30;   // (elements per launch: likewise)
