@@ -1267,9 +1267,9 @@ void launch_dwg(const moe_cfg& c, const void* x, const float* dlogits, float* dW
 namespace lmoe {
 
 // ------------------------------------------------------------- weight packing
-// Row-major [R][X] matrices -> blocked layout (bf16; R a multiple of 16, X of
-// 32), W1 and W2 in one launch.  A block takes the next eight 16 x 32 blocks of the
-// copy (n of them per matrix), which lie side by side in a strip of 16 rows (or end
+// Row-major [R][X] matrices -> blocked layout (bf16; R and X multiples of 64, so
+// that a matrix has a multiple of eight 16 x 32 blocks), W1 and W2 in one launch.  A
+// launch block takes the next eight of the copy, which lie side by side in a strip of 16 rows (or end
 // one and begin the next): it loads row pieces of 512 bytes and through LDS stores 8
 // contiguous KiB.  HBM bound: reads and writes each weight once.  Two matrices of
 // 512 MiB (d 2048, f 8192, 16 experts) 356 us, of 36 MiB (d 768, f 3072) 22.2, of
@@ -1277,7 +1277,7 @@ namespace lmoe {
 // per matrix, 377, 23.8 and 186; 128 columns of one strip per block 386, 22.2 and 195.
 __global__ __launch_bounds__(512) void pack_blocked_kernel(const uint16_t* __restrict__ W1, uint16_t* __restrict__ P1,
                                                            uint32_t X1, int64_t n1, const uint16_t* __restrict__ W2,
-                                                           uint16_t* __restrict__ P2, uint32_t X2, uint32_t n) {
+                                                           uint16_t* __restrict__ P2, uint32_t X2) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[8 * 512];
   const bool one = blockIdx.x < n1;
   const uint32_t t0 = (uint32_t)(one ? blockIdx.x : blockIdx.x - n1) * 8;
@@ -1286,13 +1286,11 @@ __global__ __launch_bounds__(512) void pack_blocked_kernel(const uint16_t* __res
   const uint32_t X = one ? X1 : X2, kb = X / 32;
   const uint32_t j = threadIdx.x % 32 / 4, r = threadIdx.x / 32, c = threadIdx.x % 4 * 8;
   const uint32_t t = t0 + j, rb = t / kb;
-  u32x4 v = u32x4{0u, 0u, 0u, 0u};
-  if (t < n) v = *reinterpret_cast<const u32x4*>(src + ((int64_t)rb * 16 + r) * X + (t - rb * kb) * 32 + c);
-  *reinterpret_cast<u32x4*>(tile + j * 512 + r * 32 + c) = v;
+  *reinterpret_cast<u32x4*>(tile + j * 512 + r * 32 + c) =
+      *reinterpret_cast<const u32x4*>(src + ((int64_t)rb * 16 + r) * X + (t - rb * kb) * 32 + c);
   __syncthreads();
-  if (t0 + (threadIdx.x >> 6) < n)
-    *reinterpret_cast<u32x4*>(dst + (int64_t)t0 * 512 + threadIdx.x * 8) =
-        *reinterpret_cast<const u32x4*>(tile + threadIdx.x * 8);
+  *reinterpret_cast<u32x4*>(dst + (int64_t)t0 * 512 + threadIdx.x * 8) =
+      *reinterpret_cast<const u32x4*>(tile + threadIdx.x * 8);
 }
 
 // Plain copies of n 16-byte elements, W1 by the first b1 blocks and W2 by the
@@ -1315,10 +1313,10 @@ void launch_pack_weights(const moe_cfg& c, const void* W1, const void* W2, void*
   const size_t bytes = (size_t)(E * f * d) * (c.dtype == MOE_BF16 ? 2 : 4);
   const bool over = (uintptr_t)W2p < (uintptr_t)W1 + bytes && (uintptr_t)W1 < (uintptr_t)W2p + bytes;
   if (c.dtype == MOE_BF16) {
-    const int64_t n = E * f * d / 512, nb = (n + 7) / 8;   // (far below 2^32: four such matrices fit the card)
+    const int64_t nb = E * f * d / 4096;
     auto go = [&](int64_t b1, int64_t b2) {
       hipLaunchKernelGGL(pack_blocked_kernel, dim3((unsigned)(b1 + b2)), dim3(512), 0, s, (const uint16_t*)W1,
-                         (uint16_t*)W1p, (uint32_t)d, b1, (const uint16_t*)W2, (uint16_t*)W2p, (uint32_t)f, (uint32_t)n);
+                         (uint16_t*)W1p, (uint32_t)d, b1, (const uint16_t*)W2, (uint16_t*)W2p, (uint32_t)f);
     };
     if (2 * nb <= 1 << 22 && !over) {
       go(nb, nb);

@@ -1,6 +1,6 @@
 """moe_pack_weights at its edges: the float copy of a few elements and of a last
 part-filled block, the bf16 blocks of matrices whose strips of 16 rows end with a
-launch block's eight, inside them and at the end of the copy."""
+launch block's eight and inside them."""
 from __future__ import annotations
 
 import pytest
