@@ -297,9 +297,11 @@ static int tile_m(const WideCall& w, int cus) {
 // Routed groups may be skewed, which shows on the device only; there the longest
 // group's tiles are the time, and smaller ones share them between CUs (Zipf 1.2,
 // capacity twice the mean of 4096 rows: 256 large tiles of 8 experts 152 and 191 us,
-// of 64 experts 174 and 194; 512 large tiles 239 and 245, of 1024 rows 72 and 74).  So
-// up to one and a half rounds, and where an idle launch (3 us) is little, both
-// shapes are launched and the row counts pick the one that runs.
+// of 64 experts 174 and 194; 512 large tiles 239 and 245, of 1024 rows 72 and 74; 64
+// experts of d 832, f 512, 512 large tiles in part-filled columns, 182 and 218).  So up
+// to one and a half rounds, and up to two where an idle launch (3 us) is little
+// against the product, both shapes are launched and the row counts pick the one that
+// runs.
 // The dense weight gradients' groups are token ranges of one length (w.expect): where
 // they are not short, 128-tiles take 3/4 of the time of a 256-tile round for the work
 // of 192 large tiles.  dW of 256 large tiles and 8192 rows each, 128- against
@@ -337,7 +339,7 @@ static TileK tile_k(const WideCall& w, int cus) {
     return r <= 1. ? 440. : r <= 2. ? 260. + 180. * r : 160. + 230. * r;
   });
   if (c128 <= c256) return kTileK128;
-  return 2 * large <= 3 * cus ? kTileKByRows : kTileK256;
+  return 2 * large <= 3 * cus || c256 >= 1e5 ? kTileKByRows : kTileK256;
 }
 static void run_wide_any(const WideCall& w, hipStream_t s) {
   if (w.rows <= 0 || w.cols <= 0 || w.groups <= 0) return;
