@@ -283,13 +283,16 @@ static int tile_m(const WideCall& w, int cus) {
 // The tile of a ragged-K product: 128 or 256 wide.  A tile is as long as its group
 // and its blocks stay on the CUs, so whole rounds decide: 256-tiles one per CU,
 // 128-tiles three.  Modelled, in ns per 32 rows of a group: a round of 256-tiles 720
-// to half full, 900 full; of 128-tiles 440 at one per CU, 620 at two, 850 at three;
-// 4000 and 2000 for a round's stores, 8000 and 7000 once.  Below 512 rows per group
-// the choice is worth 2 us at most, and 128-tiles run.
+// to half full, 900 full; of 128-tiles 440 where no CU has more than one, 620 two, 850
+// three in several rounds and 1000 in a single one (780 with at most 128 operand
+// slices of 128, which the L2s then share); 4000 and 2000 for a round's stores, 8000
+// and 7000 once, 3000 for an idle launch.  Below 512 rows per group the choice is
+// worth 2 us at most, and 128-tiles run.
 //
 // Measured on one MI355X, one product, 128- against 256-tiles: 128 large tiles of
-// 2048 rows (d 512, f 2048, 8 experts) 46 and 57 us; 192 (d 768) of 512 rows 25 and
-// 27, of 4096 132 and 119; 240 (d 640, f 1280, 16 experts) of 2048 122 and 81; 256 (d
+// 2048 rows (d 512, f 2048, 8 experts) 46 and 57 us; 160 of 11506 rows (d 192, f 2560,
+// 16 experts) 350 and 297; 192 (d 768) of 512 rows 25 and 27, of 4096 132 and 119, (d
+// 2048, 3 experts) of 2048 55 and 60; 240 (d 640, f 1280, 16 experts) of 2048 122 and 81; 256 (d
 // 1024) of 200 20 and 19, of 1024 50 and 41, of 8192 343 and 239; 288 (d 768, f 3072)
 // of 512 34 and 38, of 8192 387 and 405; 384 of 512 39 and 40, of 8192 449 and 409;
 // 512 of 1024 88 and 73.  Past two rounds of 256-tiles they win or tie at any length.
@@ -329,16 +332,16 @@ static TileK tile_k(const WideCall& w, int cus) {
   }
   if (w.expect < 512.) return kTileK128;
   const double steps = w.expect / 32.;
-  // rounds of `per` tiles: full ones, and the last by its share per CU
-  auto cost = [&](int64_t n, int64_t per, double full, double store, auto part) {
-    const int64_t rounds = n / per, rem = n % per;
-    return rounds * (steps * full + store) + (rem ? steps * part((double)rem / cus) + store : 0.);
+  auto cost = [&](int64_t n, int64_t per, double full, double store, double last) {
+    return n / per * (steps * full + store) + (n % per ? steps * last + store : 0.);
   };
-  const double c256 = 8000. + cost(large, cus, 900., 4000., [](double r) { return r <= 0.5 ? 720. : 540. + 360. * r; });
-  const double c128 = 7000. + cost(tiles(128), 3 * cus, 850., 2000., [](double r) {
-    return r <= 1. ? 440. : r <= 2. ? 260. + 180. * r : 160. + 230. * r;
-  });
-  if (c128 <= c256) return kTileK128;
+  const double fill = (double)(large % cus) / cus;
+  const double c256 = 8000. + cost(large, cus, 900., 4000., fill <= 0.5 ? 720. : 540. + 360. * fill);
+  const int64_t small = tiles(128), per = 3 * cus, rem = small % per;
+  const int64_t slices = ((w.rows + 127) / 128 + (w.cols + 127) / 128) * w.groups;
+  const double three = small > per ? 850. : slices <= 128 ? 780. : 1000.;
+  const double c128 = 7000. + cost(small, per, three, 2000., rem <= cus ? 440. : rem <= 2 * cus ? 620. : three);
+  if (c128 <= c256 + 3000.) return kTileK128;
   return 2 * large <= 3 * cus || c256 >= 1e5 ? kTileKByRows : kTileK256;
 }
 static void run_wide_any(const WideCall& w, hipStream_t s) {
